@@ -279,9 +279,9 @@ int ks_energy(ks_grid *g, const void *d_psi, const double *d_vion, double t,
 
 /* Launch shape of the H.psi kernel: a workgroup owns tile_rows full x-rows
  * of one state and marches through zchunk z-planes; each thread marches
- * rows_per_thread (1 or 2) rows of the tile, ceil(tile_rows /
- * rows_per_thread) apart.  0 keeps the library's choice for that
- * parameter.  KS_E_ARG / KS_E_UNSUPPORTED if the shape does not fit (at
+ * rows_per_thread (1 or 2) adjacent rows of the tile.  0 keeps the library's
+ * choice for that parameter; with all three 0 (the default) a call on some
+ * of the states takes the library's choice for that many states.  KS_E_ARG / KS_E_UNSUPPORTED if the shape does not fit (at
  * most 512 threads of nx * ceil(tile_rows / rows_per_thread), 160 KiB of
  * LDS, 16 halo loads per thread (8 with two rows)).  The workspace size does
  * not depend on the shape.  States, dipoles and densities do not depend on

@@ -78,6 +78,9 @@ struct ks_grid {
 
     // launch shape
     int TY = 1, zchunk = 1, ntile_y = 1, nzc = 1, rpt = 1;
+    bool auto_shape = false;    // the library's choice (no caller's shape)
+    // its choice for H.psi calls on the states of one k-point
+    int call_TY = 0, call_zchunk = 0, call_rpt = 0;
 
     // device bytes of the tables allocated by dev_alloc
     size_t owned_bytes = 0;
@@ -418,9 +421,7 @@ size_t lds_for(const ks_grid *g, int TY, int zchunk)
                           g->mixed);
 }
 
-// Launch shape: rows per tile TY (up to 512 threads, one or two rows per
-// thread) and planes per z-chunk (the full z extent unless that leaves fewer
-// than ~4 workgroups per CU).  Either may be forced (> 0) by the caller.
+// Whether a tile of TY rows with rpt rows per thread fits the kernel.
 bool tile_ok(const ks_grid *g, int TY, int rpt)
 {
     const Geo &G = g->geo;
@@ -431,15 +432,105 @@ bool tile_ok(const ks_grid *g, int TY, int rpt)
         return false;
     // the kernel holds at most 16 halo loads per thread and plane (8 when
     // it marches two rows per thread)
-    const int dyn = 2 * kHalf * G.nx +
-                    (G.per[0] ? 2 * kHalf * (TY + 2 * kHalf) : 0);
-    const int hm = (dyn + nthr - 1) / nthr;
+    const int hm = (halo_loads(G, TY) + nthr - 1) / nthr;
     return hm <= (rpt == 2 ? 8 : 16);
+}
+
+struct Shape {
+    int TY = 0, zchunk = 0, rpt = 0;
+};
+
+// The launch shape for ns states: the one with the least modelled time.  A
+// workgroup of w wavefronts takes a fixed start (tables, first planes: 2.5
+// us) and a time per plane that grows with the wavefronts resident on its CU;
+// the launch takes that for every round of workgroups over the 256 CUs.  A
+// chunk of zc planes marches zc + 4 (the last four only complete outputs).
+// The constants are fits to one pass on MI355X (us per plane at 3 / 5 / 8
+// resident wavefronts: FP64 0.6 / 0.8 / 1.05 with one row per thread, - /
+// 1.35 / 1.9 with two; FP32 0.58 / 0.68 / 0.8 and 1.1 / 1.1 / 1.25), the
+// halo term the difference of 8 and 16-row tiles at 64^3.  Few states and
+// small grids thus get short chunks of low tiles (24^3 x 4 states, 4 -> 192
+// workgroups: 40 -> 6 us per pass), large ones tall tiles of the whole axis.
+// rpt_only > 0 restricts the rows per thread (the current's kernel has one).
+Shape pick_shape(const ks_grid *g, int ns, int rpt_only = 0)
+{
+    const Geo &G = g->geo;
+    const bool mx = g->mixed && rpt_only == 0;
+    constexpr int kCUs = 256;
+    Shape best;
+    double t_best = 1e300;
+    for (int rpt = 1; rpt <= 2; ++rpt) {
+        if (rpt_only > 0 && rpt != rpt_only)
+            continue;
+        // time per plane a + b * resident wavefronts
+        const double pa = mx ? (rpt == 1 ? 0.45 : 0.85)
+                             : (rpt == 1 ? 0.42 : 0.50);
+        const double pb = mx ? (rpt == 1 ? 0.052 : 0.05)
+                             : (rpt == 1 ? 0.08 : 0.17);
+        for (int nt = 1, last = 0; nt <= G.ny; ++nt) {
+            const int TY = (G.ny + nt - 1) / nt;
+            if (TY == last || TY < rpt || !tile_ok(g, TY, rpt))
+                continue;
+            last = TY;
+            const int nthr = hpsi_threads(G.nx, TY, rpt);
+            const int w = nthr / 64;
+            const int ntile = (G.ny + TY - 1) / TY;
+            const double halo = 1.0 + 0.1 * (8.0 / TY - 0.5);
+            const bool spills = !mx && rpt == 2 &&
+                                hpsi_halo_per_thread(G, TY, nthr) > 2;
+            for (int nz = 1, lastz = 0; nz <= G.nz; ++nz) {
+                const int zc = (G.nz + nz - 1) / nz;
+                if (zc == lastz)
+                    continue;
+                lastz = zc;
+                const size_t lds =
+                    rpt_only > 0 ? hpsi_lds_bytes(G.nx, TY, zc, false)
+                                 : lds_for(g, TY, zc);
+                if (lds > kLdsBudget)
+                    continue;
+                const long nwg = (long)ntile * ((G.nz + zc - 1) / zc) * ns;
+                // wavefronts a CU holds (registers): four or three per SIMD
+                // with one row per thread (FP32, FP64), two with two
+                const int room = rpt == 2 ? 8 : (mx ? 16 : 12);
+                const int fit = std::max(
+                    1, std::min(room / std::max(1, w),
+                                (int)(kLdsBudget / lds)));
+                const long per_cu = std::min<long>(
+                    fit, (nwg + kCUs - 1) / kCUs);
+                const long rounds = (nwg + kCUs * fit - 1) / (kCUs * fit);
+                const double plane = (pa + pb * (double)(per_cu * w)) * halo *
+                                     (spills ? 1.3 : 1.0);
+                const double t = rounds * (2.5 + (zc + 4) * plane);
+                if (t < t_best) {
+                    t_best = t;
+                    best.TY = TY;
+                    best.zchunk = zc;
+                    best.rpt = rpt;
+                }
+                // more chunks of a launch that fills the chip several times
+                // over only re-read more planes
+                if (nwg > 8L * kCUs * fit)
+                    break;
+            }
+        }
+    }
+    return best;
 }
 
 int set_tiles(ks_grid *g, int TY, int zchunk, int rpt)
 {
     const Geo &G = g->geo;
+    g->auto_shape = TY <= 0 && zchunk <= 0 && rpt <= 0;
+    if (g->auto_shape) {
+        const Shape s = pick_shape(g, g->stot);
+        TY = s.TY;
+        zchunk = s.zchunk;
+        rpt = s.rpt;
+        const Shape c = pick_shape(g, g->ns);
+        g->call_TY = c.TY;
+        g->call_zchunk = c.zchunk;
+        g->call_rpt = c.rpt;
+    }
     const bool auto_rpt = rpt <= 0, auto_ty = TY <= 0;
     if (auto_rpt)
         rpt = (TY > 0 && G.nx * TY <= kRowThreads) ? 1 : (g->mixed ? 1 : 2);
@@ -616,6 +707,27 @@ HArgs base_hargs(ks_grid *g)
 {
     HArgs a;
     a.geo = g->geo;
+    // half-width-4 central weights: Laplacian (c0..c4), gradient (d1..d4)
+    static const double lap[5] = {-205.0 / 72.0, 8.0 / 5.0, -1.0 / 5.0,
+                                  8.0 / 315.0, -1.0 / 560.0};
+    static const double grad[5] = {0.0, 4.0 / 5.0, -1.0 / 5.0, 4.0 / 105.0,
+                                   -1.0 / 280.0};
+    for (int ax = 0; ax < 3; ++ax) {
+        const double h = g->geo.h[ax];
+        for (int m = 1; m <= 4; ++m) {
+            a.cl[ax][m - 1] = -0.5 * lap[m] / (h * h);
+            a.cg[ax][m - 1] = grad[m] / h;
+        }
+        a.c0 += -0.5 * lap[0] / (h * h);
+    }
+    // the weights sum to zero; rounded one by one they leave up to an ulp of
+    // c0, a shift of every energy that the taps at distance 2 take up
+    long double rest = a.c0;
+    for (int ax = 0; ax < 3; ++ax)
+        for (int m = 0; m < 4; ++m)
+            rest += 2.0L * (long double)a.cl[ax][m];
+    for (int ax = 0; ax < 3; ++ax)
+        a.cl[ax][1] = (double)((long double)a.cl[ax][1] - rest / 6.0L);
     a.kph = g->d_kph;
     a.nstates = g->ns;
     a.wocc = g->d_wocc;
@@ -631,6 +743,33 @@ HArgs base_hargs(ks_grid *g)
     a.ntile_y = g->ntile_y;
     a.nzc = g->nzc;
     return a;
+}
+
+void use_shape(const ks_grid *g, const Shape &s, HArgs *a)
+{
+    a->TY = s.TY;
+    a->rpt = s.rpt;
+    a->zchunk = s.zchunk;
+    a->ntile_y = (g->geo.ny + s.TY - 1) / s.TY;
+    a->nzc = (g->geo.nz + s.zchunk - 1) / s.zchunk;
+}
+
+// The shape of an H.psi call on ns of the states of a k-point: where the
+// library chose the grid's shape (for all of them), its choice for ns.
+void call_shape(const ks_grid *g, int ns, HArgs *a)
+{
+    if (!g->auto_shape || ns <= 0)
+        return;
+    Shape s;
+    if (ns == g->ns) {
+        s.TY = g->call_TY;
+        s.zchunk = g->call_zchunk;
+        s.rpt = g->call_rpt;
+    } else {
+        s = pick_shape(g, ns);
+    }
+    if (s.TY > 0)
+        use_shape(g, s, a);
 }
 
 GArgs base_gargs(ks_grid *g)
@@ -730,7 +869,6 @@ int exp_chain(ks_grid *g, hipStream_t st, int s0, int ns, const double2 *in,
             KS_HIP(launch_kbapply(mx, ga, ns, st));
         }
         a.in = cur;
-        a.cre = 0.0;
         a.cim = -tau / j;
         if (j < 4) {
             a.out = tb[j - 1];
@@ -849,6 +987,7 @@ int apply_h_core(ks_grid *g, const void *d_psi, void *d_hpsi, int k, int s0,
         KS_HIP(launch_kbapply(g->mixed, ga, ns, g->stream));
     }
     HArgs a = base_hargs(g);
+    call_shape(g, ns, &a);
     a.in = d_psi;
     a.out = d_hpsi;
     a.v = g->d_v;
@@ -1200,26 +1339,16 @@ int ks_current(ks_grid *g, const void *d_psi, double t, double out_host[3])
     int rc = need_ws(g);
     if (rc)
         return rc;
-    // stencil part: the H.psi kernel's tiles (one row per thread, the
-    // tallest tile within 512 threads and the default LDS share), each
+    // stencil part: the H.psi kernel's tiles (one row per thread), each
     // writing its three partial sums
-    const Geo &G = g->geo;
-    int TY = std::max(1, std::min(G.ny, kRowThreads / G.nx));
-    while (TY > 1 && (!tile_ok(g, TY, 1) ||
-                      hpsi_lds_bytes(G.nx, TY, g->zchunk, false) >
-                          kLdsDefault))
-        --TY;
-    if (!tile_ok(g, TY, 1) ||
-        hpsi_lds_bytes(G.nx, TY, g->zchunk, false) > kLdsBudget)
+    const Shape sh = pick_shape(g, g->stot, 1);
+    if (sh.TY < 1)
         return fail(KS_E_UNSUPPORTED, "no tile shape for the current");
     HArgs h = base_hargs(g);
+    use_shape(g, sh, &h);
     h.rowinfo = nullptr;
     h.W = nullptr;
     h.in = d_psi;
-    h.TY = TY;
-    h.rpt = 1;
-    h.ntile_y = (G.ny + TY - 1) / TY;
-    h.nzc = (G.nz + g->zchunk - 1) / g->zchunk;
     h.sg0 = 0;
     double A[3];
     laser_A(g, t, A);
@@ -1412,6 +1541,7 @@ int ks_energy(ks_grid *g, const void *d_psi, const double *d_vion, double t,
         KS_HIP(launch_gather(false, true, ga, g->ns, g->stream));
         KS_HIP(launch_kbapply(false, ga, g->ns, g->stream));
         HArgs a = base_hargs(g);
+        call_shape(g, g->ns, &a);
         a.in = ga.in;
         a.out = hp + (size_t)k * g->ns * N;
         a.v = d_vion;
@@ -1491,9 +1621,11 @@ int ks_set_launch(ks_grid *g, int tile_rows, int zchunk, int rows_per_thread)
     if (!g)
         return fail(KS_E_ARG, "grid is NULL");
     const int oldTY = g->TY, oldz = g->zchunk, oldr = g->rpt;
+    const bool old_auto = g->auto_shape;
     int rc = set_tiles(g, tile_rows, zchunk, rows_per_thread);
     if (rc) {
         set_tiles(g, oldTY, oldz, oldr);
+        g->auto_shape = old_auto;
         return rc;
     }
     layout(g);
@@ -1542,6 +1674,7 @@ int ks_autotune(ks_grid *g, const void *d_psi, int reps, int out_shape[3],
     if (zcs.empty())
         zcs.push_back(G.nz);
     const int oldTY = g->TY, oldz = g->zchunk, oldr = g->rpt;
+    const bool old_auto = g->auto_shape;
     // valid W for the timed passes: projector coefficients of psi
     GArgs ga = base_gargs(g);
     ga.D = g->ws + g->lay.D;
@@ -1572,7 +1705,6 @@ int ks_autotune(ks_grid *g, const void *d_psi, int reps, int out_shape[3],
         HArgs a = base_hargs(g);
         a.v = g->d_v;
         a.v32 = wsp<float>(g, g->lay.v32);
-        a.cre = 0.0;
         // a grid with a laser runs the passes with the gradient term: time
         // that kernel, at the pulse's amplitude
         if (g->laser[0] != 0.0) {
@@ -1630,10 +1762,12 @@ int ks_autotune(ks_grid *g, const void *d_psi, int reps, int out_shape[3],
                 rc = run(sh.first, zc, sh.second);
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    if (rc)
+    if (rc) {
         set_tiles(g, oldTY, oldz, oldr);
-    else
+        g->auto_shape = old_auto;
+    } else {
         set_tiles(g, bestTY, bestz, bestr);
+    }
     layout(g);
     if (rc)
         return rc;
@@ -2336,8 +2470,7 @@ int ks_batch_create(const ks_job *jobs, int njobs, void *stream,
             a.v = e == 0 ? J.vcur : (J.nonlin ? J.vpred : J.vion);
             a.v32 = mixed ? wsp<float>(b->grids[i], b->grids[i]->lay.v32)
                           : nullptr;
-            a.cre = 0.0;
-            a.cim = -0.5 * J.dt / j;
+                a.cim = -0.5 * J.dt / j;
             if (j < 4) {
                 a.out = J.t[j - 1];
             } else {

@@ -3,13 +3,6 @@
 #ifndef KS_HPSI_PART
 #define KS_HPSI_PART 0
 #endif
-// Planes the H.psi kernel's loads run ahead: the FP64 kernels (part 0)
-// keep one register set (fewer registers; measured faster at 64^3, 48^3
-// and 128^3), the mixed ones two alternating sets.
-#ifndef KS_HPSI_PF
-#define KS_HPSI_PF (KS_HPSI_PART == 0 ? 1 : 2)
-#endif
-
 #include "ks_device.h"
 
 #include <algorithm>
@@ -70,7 +63,7 @@ __device__ __forceinline__ const void *pass_input(cptr_t<JobDev> J, int p)
 #ifndef KS_BATCH_REMAP
 #define KS_BATCH_REMAP 1
 #endif
-template <class R, class InT, class TT, int MODE, bool GRAD, int HM, int RPT>
+template <class R, class InT, class TT, int MODE, int GRAD, int HM, int RPT>
 __global__ __launch_bounds__(512) void k_hpsi_batch(BArgs b)
 {
     const int total = cp(b.off)[b.njobs];
@@ -179,7 +172,7 @@ int batch_items(int kind, const JobDev &J)
 
 #endif
 
-template <class R, class InT, class TT, int MODE, bool GRAD>
+template <class R, class InT, class TT, int MODE, int GRAD>
 static hipError_t go_hpsi_batch(const BArgs &b, int hm, int rpt, int nthr,
                                 size_t lds, int grid, hipStream_t st)
 {
@@ -221,9 +214,9 @@ static hipError_t go_hpsi_batch_g(const BArgs &b, bool grad, int hm, int rpt,
                                   int nthr, size_t lds, int grid,
                                   hipStream_t st)
 {
-    return grad ? go_hpsi_batch<R, InT, TT, MODE, true>(b, hm, rpt, nthr,
+    return grad ? go_hpsi_batch<R, InT, TT, MODE, 1>(b, hm, rpt, nthr,
                                                         lds, grid, st)
-                : go_hpsi_batch<R, InT, TT, MODE, false>(b, hm, rpt, nthr,
+                : go_hpsi_batch<R, InT, TT, MODE, 0>(b, hm, rpt, nthr,
                                                          lds, grid, st);
 }
 

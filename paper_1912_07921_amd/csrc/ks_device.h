@@ -13,8 +13,8 @@
 // Stencil design (HBM bound: 32 B moved per point and state in FP64):
 //  - a workgroup owns a tile of full x-rows (nx x TY) of one state and marches
 //    along z over a chunk of planes;
-//  - each thread keeps the 9-deep z-column of its point in registers, so every
-//    value is loaded from memory once per pass (plus the y-halo rows);
+//  - each thread keeps the z-neighbours' share of its points in registers, so
+//    every value is loaded from memory once per pass (plus the y-halo rows);
 //  - the current xy plane (with 4 halo rows on each side) is staged in LDS for
 //    the x and y neighbours; x-rows are read as consecutive 16-byte complex
 //    values across the wavefront (coalesced);
@@ -34,16 +34,11 @@
 
 namespace ks {
 
-// Planes of lead of the H.psi kernel's loads (1 or 2, see hpsi_item).
-#ifndef KS_HPSI_PF
-#define KS_HPSI_PF 2
-#endif
-
 // Half-width-4 central weights: Laplacian (c0..c4) and gradient (d1..d4).
-static __constant__ double kLap[5] = {-205.0 / 72.0, 8.0 / 5.0, -1.0 / 5.0,
-                                      8.0 / 315.0, -1.0 / 560.0};
-static __constant__ double kGrad[5] = {0.0, 4.0 / 5.0, -1.0 / 5.0,
-                                       4.0 / 105.0, -1.0 / 280.0};
+constexpr double kLap[5] = {-205.0 / 72.0, 8.0 / 5.0, -1.0 / 5.0, 8.0 / 315.0,
+                            -1.0 / 560.0};
+constexpr double kGrad[5] = {0.0, 4.0 / 5.0, -1.0 / 5.0, 4.0 / 105.0,
+                             -1.0 / 280.0};
 
 template <class R> struct Cplx;
 template <> struct Cplx<double> { using T = double2; };
@@ -98,6 +93,54 @@ template <class V> __device__ __forceinline__ V cmulc(V a, V b)
     r.x = a.x * b.x + a.y * b.y;
     r.y = a.y * b.x - a.x * b.y;
     return r;
+}
+
+// Fused multiply-adds written out, so that every kernel that forms a value
+// rounds it alike; acc + s a for a complex a.
+__device__ __forceinline__ double rfma(double a, double b, double c)
+{
+    return __builtin_fma(a, b, c);
+}
+__device__ __forceinline__ float rfma(float a, float b, float c)
+{
+    return __builtin_fmaf(a, b, c);
+}
+template <class V, class S> __device__ __forceinline__ V cfma(S s, V a, V acc)
+{
+    acc.x = rfma(s, a.x, acc.x);
+    acc.y = rfma(s, a.y, acc.y);
+    return acc;
+}
+// a b with its roundings fixed (every kernel that applies a phase gets the
+// same bits)
+template <class V> __device__ __forceinline__ V cmulf(V a, V b)
+{
+    V r;
+    r.x = rfma(a.x, b.x, -(a.y * b.y));
+    r.y = rfma(a.y, b.x, a.x * b.y);
+    return r;
+}
+// A copy the optimiser cannot trace: what is computed from it inside a loop
+// stays in the loop (the LDS addresses of the H.psi kernel would otherwise be
+// hoisted into tens of vector registers and spill).
+__device__ __forceinline__ int fresh(int s)
+{
+    asm volatile("" : "+s"(s));
+    return s;
+}
+// A value that is the same in every lane, moved to scalar registers.
+__device__ __forceinline__ float uni(float v)
+{
+    return __builtin_bit_cast(
+        float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ double uni(double v)
+{
+    typedef int i2 __attribute__((ext_vector_type(2)));
+    i2 b = __builtin_bit_cast(i2, v);
+    b.x = __builtin_amdgcn_readfirstlane(b.x);
+    b.y = __builtin_amdgcn_readfirstlane(b.y);
+    return __builtin_bit_cast(double, b);
 }
 
 // Every buffer the kernels touch is global memory.  Accesses go through an
@@ -236,73 +279,85 @@ __device__ __forceinline__ typename Cplx<R>::T ldc_g(const T *p, long i)
 // beyond the buffer's size reads zero and drops a store, so an access with
 // nothing to move needs no branch around it.
 typedef __amdgpu_buffer_rsrc_t BufRes;
-__device__ __forceinline__ BufRes buf_res(const void *p, size_t bytes)
+__device__ __forceinline__ BufRes buf_res(const void *p, int bytes)
 {
-    return __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<void *>(p), (short)0,
-        (int)(bytes < 0x7fffffffUL ? bytes : 0x7fffffffUL), 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), (short)0,
+                                             bytes, 0x00020000);
 }
-template <class T> __device__ __forceinline__ T bld_raw(BufRes r, unsigned off);
-template <> __device__ __forceinline__ double2 bld_raw<double2>(BufRes r,
-                                                                unsigned off)
+// A buffer of any size below 2 GiB whose accesses keep their own bounds
+// (kBufNone: nothing to move), or an empty one (use == false).
+constexpr unsigned kBufNone = 0x80000000u;
+__device__ __forceinline__ BufRes buf_any(const void *p, bool use)
 {
-    return __builtin_bit_cast(double2,
-                              __builtin_amdgcn_raw_buffer_load_b128(r, off, 0,
-                                                                    0));
+    return buf_res(p, use ? 0x7fffffff : 0);
 }
-template <> __device__ __forceinline__ float2 bld_raw<float2>(BufRes r,
-                                                              unsigned off)
+// off is the per-thread byte offset (range checked against the buffer's
+// size), soff a byte offset uniform over the wavefront (added to the address
+// past the check).
+template <class T>
+__device__ __forceinline__ T bld_raw(BufRes r, unsigned off, int soff);
+template <>
+__device__ __forceinline__ double2 bld_raw<double2>(BufRes r, unsigned off,
+                                                    int soff)
 {
-    return __builtin_bit_cast(float2,
-                              __builtin_amdgcn_raw_buffer_load_b64(r, off, 0,
-                                                                   0));
+    return __builtin_bit_cast(
+        double2, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0));
+}
+template <>
+__device__ __forceinline__ float2 bld_raw<float2>(BufRes r, unsigned off,
+                                                  int soff)
+{
+    return __builtin_bit_cast(
+        float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0));
 }
 // the same with the non-temporal hint (streams read once)
-#ifndef KS_NT_ONCE
-#define KS_NT_ONCE 1
-#endif
 template <class T>
-__device__ __forceinline__ T bld_raw_nt(BufRes r, unsigned off);
+__device__ __forceinline__ T bld_raw_nt(BufRes r, unsigned off, int soff);
 template <>
-__device__ __forceinline__ double2 bld_raw_nt<double2>(BufRes r, unsigned off)
+__device__ __forceinline__ double2 bld_raw_nt<double2>(BufRes r, unsigned off,
+                                                       int soff)
 {
     return __builtin_bit_cast(
-        double2, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0,
-                                                       KS_NT_ONCE ? 2 : 0));
+        double2, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 2));
 }
 template <>
-__device__ __forceinline__ float2 bld_raw_nt<float2>(BufRes r, unsigned off)
+__device__ __forceinline__ float2 bld_raw_nt<float2>(BufRes r, unsigned off,
+                                                     int soff)
 {
     return __builtin_bit_cast(
-        float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0,
-                                                     KS_NT_ONCE ? 2 : 0));
+        float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 2));
 }
-// complex value of storage type T at byte offset off, in precision R
+// complex value of storage type T, in precision R
 template <class R, class T>
-__device__ __forceinline__ typename Cplx<R>::T bld(BufRes r, unsigned off)
+__device__ __forceinline__ typename Cplx<R>::T bld(BufRes r, unsigned off,
+                                                   int soff)
 {
-    const T v = bld_raw<T>(r, off);
+    const T v = bld_raw<T>(r, off, soff);
     typename Cplx<R>::T o;
     o.x = (R)v.x;
     o.y = (R)v.y;
     return o;
 }
 template <class R, class T>
-__device__ __forceinline__ typename Cplx<R>::T bld_nt(BufRes r, unsigned off)
+__device__ __forceinline__ typename Cplx<R>::T bld_nt(BufRes r, unsigned off,
+                                                      int soff)
 {
-    const T v = bld_raw_nt<T>(r, off);
+    const T v = bld_raw_nt<T>(r, off, soff);
     typename Cplx<R>::T o;
     o.x = (R)v.x;
     o.y = (R)v.y;
     return o;
 }
-__device__ __forceinline__ double bld_d(BufRes r, unsigned off)
+__device__ __forceinline__ double bld_d(BufRes r, unsigned off, int soff)
 {
-    return __builtin_bit_cast(double,
-                              __builtin_amdgcn_raw_buffer_load_b64(r, off, 0,
-                                                                   0));
+    return __builtin_bit_cast(
+        double, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0));
 }
-// non-temporal stores (the outputs are read by the next pass only)
+// Non-temporal stores (the outputs are read by the next pass only).  No
+// scalar offset: the compiler leaves no wait state between a 16-byte store
+// that has one and the next write of its data registers, and on gfx950 such
+// a store was seen to take the overwritten data; the plane goes into the
+// buffer's base address instead.
 template <class T>
 __device__ __forceinline__ void bst(BufRes r, unsigned off, double x,
                                     double y);
@@ -428,19 +483,36 @@ __device__ __forceinline__ int xcd_remap(int L, int nblk)
 // ---------------------------------------------------------------------------
 // H.psi with a fused epilogue.  R: arithmetic precision; InT: storage type of
 // the input states; TT: storage type of t-terms (t1, t2, term outputs);
-// GRAD: the velocity-gauge term -i A.grad is present; HM: halo loads per
-// thread and plane.
+// GRAD: the velocity-gauge term -i A.grad (0: none, 1: every axis, 2: A along
+// z only); HM: halo loads per thread and plane; RPT: rows per thread.
 //
-// LDS holds the current xy plane of the tile padded by 4 rows above and below
-// and 4 columns left and right: the neighbours' values, zeros (zero
-// boundary; written once) or Bloch-wrapped values.  The stencil reads its x
-// and y neighbours there without branches; the z neighbours come from a
-// per-thread register queue.  Per z-plane: one barrier, two plane buffers
-// alternating.  Every stream is fetched PF planes ahead of its use (PF = 1
-// in the FP64 kernels, 2 in the FP32 ones, whose registers allow a second
-// set): the halo of plane z+PF, the own column of plane z+4+PF, the
-// potential and the KB term of plane z+PF are in flight while plane z is
-// computed.  The KB term V_NL in is precomputed on the hull rows
+// A workgroup marches its tile of full x-rows along z.  LDS holds the current
+// xy plane padded by 4 rows above and below and 4 columns left and right: the
+// neighbours' values, zeros (zero boundary; written once) or Bloch-wrapped
+// values, so the x and y taps are branch-free LDS reads; two plane buffers
+// alternate, one barrier per plane.  A thread owns RPT adjacent rows, whose y
+// taps overlap: 9 + RPT - 1 reads serve all of them.
+// Along z the FP64 kernels split the star: plane z adds its x, y, centre and
+// z-4 .. z-1 taps to the output of plane z and its own z+m taps to the pending
+// outputs of planes z-1 .. z-4, the last of which is then complete and stored.
+// Four previous values and four pending outputs per point live in registers,
+// their slots fixed by unrolling the march by four, and a plane's own rows and
+// its halo rows are loaded at the same time, so that neighbouring tiles find
+// them in the L2 (128^3, 64 states: 4.9 -> 3.9 GB fetched per term pass).
+// Every tap is one FMA with a coefficient that carries -1/2 c_m / h^2, from
+// the smallest weight to the largest: half the rounding error of pairwise
+// sums.  The FP32 kernels keep a column of nine values and the order of their
+// sums.  Every access is a raw buffer access with a constant per-thread offset
+// and the plane in the scalar offset.
+// What bounds it: large launches memory (128^3 x 64 states FP64 term pass, 6.0
+// GB through the L2 in 1.05 ms = 5.7 TB/s, where a plain copy reaches 6.6;
+// without the x taps 1.02 ms), launches of few states the chain of barrier,
+// LDS reads, FMAs and loads of each plane (~0.6 us with one row per thread,
+// whatever is loaded), which is why those get short chunks of low tiles.
+// Loads run PF planes ahead of their use: 2, or 1 in the FP64 kernels with
+// two rows per thread, whose registers hold no second set (64^3 x 32, one row:
+// 80 -> 72 us with 2; two rows: 70 -> 127 us, spilled).  The KB term V_NL in
+// is precomputed on the hull rows
 // (k_kbapply) and added with one coalesced read.
 // ---------------------------------------------------------------------------
 extern __shared__ double2 smem_d2[];
@@ -448,16 +520,17 @@ extern __shared__ double2 smem_d2[];
 // One work item of the H.psi pass described by `a`: work item w is
 // (launch state, z-chunk, y-tile).  The whole workgroup takes part.  Avec
 // holds the vector potential (x, y, z) and |A|^2 / 2 of the pass.  Thread
-// t owns column x = t % nx of rows yl + r * TYh (r < RPT, yl = t / nx,
-// TYh = ceil(TY / RPT)): every row set is a contiguous run of the plane, so
-// loads stay coalesced while a tile of TY rows needs only TY / RPT thread
-// rows.
-template <class R, class InT, class TT, int MODE, bool GRAD, int HM, int RPT>
+// t owns column x = t % nx of the rows base .. base + rpt - 1 with base =
+// rpt * (t / nx) (the last pair of an odd tile is shifted up by one and its
+// first row left to its neighbour).
+template <class R, class InT, class TT, int MODE, int GRAD, int HM, int RPT>
 __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
                                           const double4 Avec)
 {
     using V = typename Cplx<R>::T;
     unsigned char *smem_raw = reinterpret_cast<unsigned char *>(smem_d2);
+    constexpr bool FIN = MODE == kFinal || MODE == kFinalPred;
+    constexpr bool CUR = MODE == kCurrent;
 
     const int nx = a.geo.nx, ny = a.geo.ny, nz = a.geo.nz;
     const int P = nx * ny;
@@ -475,7 +548,7 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
     const int TY = a.TY;
     // rows per thread of this item's shape (the launch's RPT is the most
     // any item of it uses)
-    const int rpt = RPT > 1 ? a.rpt : 1;
+    const int rpt = RPT > 1 ? min(a.rpt, TY) : 1;
     const int TYh = (TY + rpt - 1) / rpt;
     const int y0 = tile_y * TY;
     const int rows = min(TY, ny - y0);
@@ -484,97 +557,172 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
     const int x = tid % nx;
     const int yl = tid / nx;
     const int RS = nx + 2 * kHalf;                  // LDS row stride
-    bool act[RPT];
-    int ylr[RPT], own[RPT], po[RPT];
+    const int row0 = yl < TYh ? min(yl * rpt, TY - rpt) : 0;
+    const int own = (row0 + kHalf) * RS + x + kHalf;  // LDS slot of row 0
+    // byte offsets within a plane of 16, 8 and 4-byte elements.  A row that
+    // two threads hold is stored by both, with the same value, and counted
+    // by the one that owns it (act).
+    bool valid[RPT], act[RPT];
+    unsigned p16[RPT], p8[RPT], p4[RPT];
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
-        ylr[r] = yl + r * TYh;
-        act[r] = r < rpt && yl < TYh && ylr[r] < rows;
-        const int y = y0 + (act[r] ? ylr[r] : 0);
-        own[r] = (ylr[r] + kHalf) * RS + x + kHalf; // LDS slot of the point
-        po[r] = y * nx + x;                         // offset within a plane
+        valid[r] = r < rpt && yl < TYh && row0 + r < rows;
+        act[r] = valid[r] && row0 + r >= yl * rpt;
+        const unsigned p = (unsigned)((y0 + row0 + r) * nx + x);
+        p16[r] = valid[r] ? p * 16u : kBufNone;
+        p8[r] = valid[r] ? p * 8u : kBufNone;
+        p4[r] = valid[r] ? p * 4u : kBufNone;
     }
     const int z0 = zc * a.zchunk;
     const int z1 = min(nz, z0 + a.zchunk);
+    // FP64 scatters plane z's z taps to pending outputs, FP32 gathers them
+    // from a column of nine values (below)
+    constexpr bool SC = sizeof(R) == 8;
+    const int zend = SC && !CUR ? z1 + 4 : z1;      // planes marched
 
     const int plane = (TY + 2 * kHalf) * RS;
     V *buf0 = reinterpret_cast<V *>(smem_raw);
     V *buf1 = buf0 + plane;
     V *sPh = buf1 + plane;        // x/y wrap phases, 81 entries
     V *sPz = sPh + 81;            // z wrap phases, 9 entries
-    int4 *sRow = reinterpret_cast<int4 *>(sPz + 9);   // hull rows of tile
+    int2 *sRow = reinterpret_cast<int2 *>(sPz + 9);   // hull rows of tile
 
+    // ---- buffers.  Every per-plane access is a raw buffer access whose
+    // per-thread offset is out of range where there is nothing to move, and
+    // whose buffer is empty for a plane outside the grid or the chunk (the
+    // hardware then returns zero, or drops the store), so no memory
+    // instruction sits behind a branch and the compiler knows exactly how
+    // many are in flight.  The range check covers the per-thread offset, the
+    // plane rides in the scalar offset. ----
     const InT *in = reinterpret_cast<const InT *>(a.in) + (size_t)sl * N;
-    const bool proj = MODE != kCurrent && a.rowinfo != nullptr;
+    const bool proj = !CUR && a.rowinfo != nullptr;
     const V *Wst = reinterpret_cast<const V *>(a.W) + (size_t)sl * a.nhull;
+    const size_t sN = (size_t)sl * N;
+    // the potential: FP64, or its FP32 copy in the FP32 kernels (half the
+    // bytes of the stream every state re-reads)
+    constexpr bool V32 = sizeof(R) == 4;
+    constexpr unsigned VB = V32 ? 4u : 8u;
+    const void *vptr = CUR ? nullptr
+                           : (V32 ? (const void *)a.v32 : (const void *)a.v);
+    using OutT = typename std::conditional<MODE == kTerm, TT, double2>::type;
+    OutT *out = CUR ? nullptr : reinterpret_cast<OutT *>(a.out) + sN;
+    const BufRes rw = buf_any(Wst, proj);
+    auto off_of = [&](int r, size_t elem) -> unsigned {
+        return elem == 16 ? p16[r] : (elem == 8 ? p8[r] : p4[r]);
+    };
+
+    // plane of the grid that plane zq maps to (-1: none); the own rows are
+    // needed on planes z0 - 4 .. z1 + 3
+    auto wrap_z = [&](int zq) -> int {
+        if (perz) {
+            while (zq < 0)
+                zq += nz;
+            while (zq >= nz)
+                zq -= nz;
+        }
+        return zq >= 0 && zq < nz ? zq : -1;
+    };
+    auto own_ld = [&](int r, int zz) -> V {
+        return bld<R, InT>(buf_any(in, zz >= 0), off_of(r, sizeof(InT)),
+                           max(zz, 0) * P * (int)sizeof(InT));
+    };
+    // the own rows of plane zq as loaded, with their Bloch phase
+    auto own_fix = [&](V v, int zq) -> V {
+        if (perz && (zq < 0 || zq >= nz)) {
+            int wz = 0;
+            for (; zq < 0; zq += nz)
+                --wz;
+            for (; zq >= nz; zq -= nz)
+                ++wz;
+            v = cmulf(v, sPz[wz + 4]);
+        }
+        return v;
+    };
+    // the first planes of the column: they are in flight during the setup.
+    // FP64: p[r][s] holds plane z < z0 with (z - z0) & 3 == s; FP32: q[r][m]
+    // holds plane z + m - 4.
+    V p[RPT][4], q[RPT][9], c[RPT];
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+        if constexpr (SC) {
+#pragma unroll
+            for (int m = 1; m <= 4; ++m)
+                p[r][4 - m] = own_ld(r, wrap_z(z0 - m));
+            c[r] = own_ld(r, z0);
+        } else {
+#pragma unroll
+            for (int m = 0; m <= 8; ++m)
+                q[r][m] = own_ld(r, wrap_z(z0 - 4 + m));
+        }
+    }
 
     // ---- Bloch phases of x/y wraps by -4..4 cells: sPh[(wy+4)*9 + wx+4],
-    // of z wraps: sPz[wz+4]; hull rows of this tile: sRow[(z-z0)*TY + row] --
-    for (int t = tid; t < 81 + 9; t += nthr) {
-        V ph;
-        if (t < 81) {
-            const int wx = t % 9 - 4, wy = t / 9 - 4;
-            ph = cmk<V>(1.0, 0.0);
-            if (wx)
-                ph = cmul(ph, phase_pow<V>(kph, 0, wx));
-            if (wy)
-                ph = cmul(ph, phase_pow<V>(kph, 1, wy));
-        } else {
-            const int wz = t - 81 - 4;
-            ph = wz ? phase_pow<V>(kph, 2, wz) : cmk<V>(1.0, 0.0);
+    // of z wraps: sPz[wz+4]; hull rows of this tile: sRow[(z-z0)*TY + row] =
+    // (first x | (count - 1) << 16, hull index of x = 0), none: first x
+    // beyond the row ----
+    if (perx || pery || perz)
+        for (int t = tid; t < 81 + 9; t += nthr) {
+            V ph;
+            if (t < 81) {
+                const int wx = t % 9 - 4, wy = t / 9 - 4;
+                ph = cmk<V>(1.0, 0.0);
+                if (wx)
+                    ph = cmulf(ph, phase_pow<V>(kph, 0, wx));
+                if (wy)
+                    ph = cmulf(ph, phase_pow<V>(kph, 1, wy));
+            } else {
+                const int wz = t - 81 - 4;
+                ph = wz ? phase_pow<V>(kph, 2, wz) : cmk<V>(1.0, 0.0);
+            }
+            sPh[t] = ph;
         }
-        sPh[t] = ph;
-    }
     if (proj)
         for (int t = tid; t < (z1 - z0) * TY; t += nthr) {
             const int zz = z0 + t / TY, r = t % TY;
-            int4 ri = make_int4(1, 0, 0, 0);
-            if (r < rows)
-                ri = gld(a.rowinfo + zz * ny + y0 + r);
+            int2 ri = make_int2(0xffff, 0);
+            if (r < rows) {
+                const int4 g = gld(a.rowinfo + zz * ny + y0 + r);
+                if (g.x <= g.y)
+                    ri = make_int2(g.x | (g.y - g.x) << 16, g.z - g.x);
+            }
             sRow[t] = ri;
         }
 
-    // ---- halo of the padded plane: 8 rows of nx and 8 columns of rows+8.
-    // Both buffers start zeroed, which holds every entry outside a
-    // zero-boundary axis for all planes.  The other ("dynamic") entries are
-    // loaded per plane: the in-grid (or wrapped) halo rows, and on a
-    // periodic x axis the wrapped columns of every row with content.
-    // Dynamic entry d goes to this thread when d = tid + i * nthr, i < HM.
-    // hoff: offset within a plane (-1: none); hpk: LDS slot | phase id << 20
-    // (id 40: no wrap) ----
+    // ---- halo of the padded plane: 8 rows of nx and 8 columns of the
+    // tile's rows (the star never reads the corners).  Both buffers start
+    // zeroed, which holds every entry outside a zero-boundary axis for all
+    // planes.  The in-grid (or wrapped) halo rows are loaded per plane; the
+    // wrapped columns of a periodic x axis are copies of the tile's own
+    // values, written by the threads that hold them, or loaded where a row
+    // is shorter than both halves of the halo.  Loaded entry d goes to this thread when
+    // d = tid + i * nthr, i < HM.  hof: byte offset within a plane; hpk: LDS slot | phase id << 20 (id 40: no wrap) ----
     for (int t = tid; t < 2 * plane; t += nthr)
         buf0[t] = czero<V>();
+    const bool xcopy = perx && nx >= 2 * kHalf;
     const int u0 = pery ? 0 : max(0, kHalf - y0);   // first dynamic top row
     const int nup = kHalf - u0;
     const int nlow = pery ? kHalf : max(0, min(kHalf, ny - (y0 + rows)));
     const int ndy = (nup + nlow) * nx;
-    const int r_lo = u0, r_hi = rows + kHalf + nlow;
-    const int ndyn = ndy + (perx ? (r_hi - r_lo) * 2 * kHalf : 0);
-    int hoff[HM], hpk[HM];
+    const int ndyn = ndy + (perx && !xcopy ? rows * 2 * kHalf : 0);
+    unsigned hof[HM];
+    int hpk[HM];
 #pragma unroll
     for (int i = 0; i < HM; ++i) {
         const int d = tid + i * nthr;
-        hoff[i] = -1;
-        hpk[i] = 0;
+        hof[i] = kBufNone;
+        hpk[i] = 40 << 20;
         if (d >= ndyn)
             continue;
         int r, xs, slot;
         if (d < ndy) {
-            int hx;
-            if (d < nup * nx) {
-                r = u0 + d / nx;
-                hx = d - (d / nx) * nx;
-            } else {
-                const int d1 = d - nup * nx;
-                r = rows + kHalf + d1 / nx;
-                hx = d1 - (d1 / nx) * nx;
-            }
+            const int q = d / nx, hx = d - q * nx;
+            r = q < nup ? u0 + q : rows + kHalf + (q - nup);
             xs = hx;
             slot = r * RS + hx + kHalf;
         } else {
             const int d2 = d - ndy;
             const int cc = d2 % (2 * kHalf);
-            r = r_lo + d2 / (2 * kHalf);
+            r = kHalf + d2 / (2 * kHalf);
             xs = cc < kHalf ? cc - kHalf : nx + cc - kHalf;
             slot = r * RS + (cc < kHalf ? cc : nx + cc);
         }
@@ -588,337 +736,411 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
             wx = floordiv(xs, nx);
             xs -= wx * nx;
         }
-        hoff[i] = ys * nx + xs;
+        hof[i] = (unsigned)(ys * nx + xs) * (unsigned)sizeof(InT);
         hpk[i] = slot | (((wy + 4) * 9 + wx + 4) << 20);
     }
-    __syncthreads();   // zeroed buffers, phase tables and hull rows ready
-
-    // ---- loads and stores.  Every per-plane access is a raw buffer access
-    // whose offset is out of range where there is nothing to move (the
-    // hardware then returns zero, or drops the store), so no memory
-    // instruction sits behind a branch and the compiler knows exactly how
-    // many are in flight; the loads of plane z+2 are issued at the start of
-    // plane z into one of two register sets that alternate with the parity
-    // of z, so no register that a load is still filling is ever moved.
-    // Bloch phases are applied where a value is consumed. ----
-    constexpr unsigned kOOB = 0x80000000u;
-    const BufRes rin = buf_res(in, (size_t)N * sizeof(InT));
-    // the potential: FP64, or its FP32 copy in the FP32 kernels (half the
-    // bytes of the stream every state re-reads)
-    constexpr bool V32 = sizeof(R) == 4;
-    constexpr unsigned VB = V32 ? 4u : 8u;
-    const BufRes rv = buf_res(MODE == kCurrent
-                                  ? nullptr
-                                  : (V32 ? (const void *)a.v32
-                                         : (const void *)a.v),
-                              MODE == kCurrent ? 0 : (size_t)N * VB);
-    const BufRes rw = buf_res(Wst, proj ? (size_t)a.nhull * sizeof(V) : 0);
-    constexpr bool FIN = MODE == kFinal || MODE == kFinalPred;
-    const size_t sN = (size_t)sl * N;
-    const BufRes rbase = buf_res(FIN ? a.base + sN : nullptr,
-                                 FIN ? (size_t)N * 16 : 0);
-    const BufRes rt1 = buf_res(FIN ? reinterpret_cast<const TT *>(a.t1) + sN
-                                   : nullptr,
-                               FIN ? (size_t)N * sizeof(TT) : 0);
-    const BufRes rt2 = buf_res(FIN ? reinterpret_cast<const TT *>(a.t2) + sN
-                                   : nullptr,
-                               FIN ? (size_t)N * sizeof(TT) : 0);
-    using OutT = typename std::conditional<MODE == kTerm, TT, double2>::type;
-    const BufRes rout = buf_res(MODE == kCurrent
-                                    ? nullptr
-                                    : reinterpret_cast<OutT *>(a.out) + sN,
-                                MODE == kCurrent ? 0
-                                                 : (size_t)N * sizeof(OutT));
-    const BufRes rnp = buf_res(FIN && a.npart ? a.npart + sN : nullptr,
-                               FIN && a.npart ? (size_t)N * 8 : 0);
-
-    // byte offsets of plane zq (any integer for the own column)
-    auto col_off = [&](int r, int zq) -> unsigned {
-        int zz = zq;
-        if (zq < 0 || zq >= nz) {
-            if (!perz)
-                return kOOB;
-            zz = zq - floordiv(zq, nz) * nz;
-        }
-        return act[r] ? (unsigned)(zz * P + po[r]) * (unsigned)sizeof(InT)
-                      : kOOB;
+    auto halo_ld = [&](int i, int zq) -> V {
+        const bool ok = zq < z1;
+        return bld<R, InT>(buf_any(in, ok), hof[i],
+                           (ok ? zq * P : 0) * (int)sizeof(InT));
     };
-    // the own column of plane zq as loaded, with its Bloch phase
-    auto col_fix = [&](V v, int zq) -> V {
-        if (perz && (zq < 0 || zq >= nz))
-            v = cmul(v, sPz[floordiv(zq, nz) + 4]);
-        return v;
-    };
-    auto halo_off = [&](int i, int zq) -> unsigned {
-        return (hoff[i] >= 0 && zq < nz)
-                   ? (unsigned)(zq * P + hoff[i]) * (unsigned)sizeof(InT)
-                   : kOOB;
-    };
-    auto halo_fix = [&](int i, V v) -> V {
-        const int pid = hpk[i] >> 20;
-        return pid != 40 ? cmul(v, sPh[pid]) : v;
-    };
-    auto v_off = [&](int r, int zq) -> unsigned {
-        return (act[r] && zq < nz) ? (unsigned)(zq * P + po[r]) * VB : kOOB;
-    };
-    auto v_ld = [&](unsigned off) -> double {
+    using VV = typename std::conditional<V32, float, double>::type;
+    auto v_ld = [&](int r, int zq) -> VV {
+        const bool ok = zq >= z0 && zq < z1;
+        const BufRes rv = buf_any(vptr, ok);
+        const int so = (ok ? zq * P : 0) * (int)VB;
         if constexpr (V32)
-            return (double)__builtin_bit_cast(
-                float, __builtin_amdgcn_raw_buffer_load_b32(rv, off, 0, 0));
+            return __builtin_bit_cast(
+                float,
+                __builtin_amdgcn_raw_buffer_load_b32(rv, p4[r], so, 0));
         else
-            return bld_d(rv, off);
+            return bld_d(rv, p8[r], so);
     };
-    auto kb_off = [&](int r, int zq) -> unsigned {
-        if (!proj || !act[r] || zq >= z1)
-            return kOOB;
-        const int4 ri = sRow[(zq - z0) * TY + ylr[r]];
-        return (x >= ri.x && x <= ri.y)
-                   ? (unsigned)(ri.z + x - ri.x) * (unsigned)sizeof(V)
-                   : kOOB;
-    };
-
-    // ---- prologue: the 9-deep columns around z0, plane z0 in LDS, and
-    // the register sets: S[1] holds plane z0+1 (halo, potential, KB term)
-    // and the own column of plane z0+1+kHalf, S[0] the potential and KB
-    // term of plane z0 ----
-    V q[RPT][2 * kHalf + 1];
-#pragma unroll
-    for (int r = 0; r < RPT; ++r) {
-#pragma unroll
-        for (int m = 0; m <= 2 * kHalf; ++m)
-            q[r][m] = col_fix(bld<R, InT>(rin, col_off(r, z0 - kHalf + m)),
-                              z0 - kHalf + m);
-        if (act[r])
-            buf0[own[r]] = q[r][kHalf];
-    }
-#pragma unroll
-    for (int i = 0; i < HM; ++i) {
-        const V hv0 = bld<R, InT>(rin, halo_off(i, z0));
-        if (hoff[i] >= 0)
-            buf0[hpk[i] & 0xfffff] = halo_fix(i, hv0);
-    }
-    V shv[2][HM], snq[2][RPT], skb[2][RPT];
-    double sv[2][RPT];
-#pragma unroll
-    for (int i = 0; i < HM; ++i) {
-        shv[1][i] = bld<R, InT>(rin, halo_off(i, z0 + 1));
-        shv[0][i] = czero<V>();
-    }
-#pragma unroll
-    for (int r = 0; r < RPT; ++r) {
-        snq[1][r] = bld<R, InT>(rin, col_off(r, z0 + kHalf + 1));
-        snq[0][r] = czero<V>();
-        if (KS_HPSI_PF == 2) {
-            sv[1][r] = v_ld(v_off(r, z0 + 1));
-            sv[0][r] = v_ld(v_off(r, z0));
-            skb[1][r] = bld_nt<R, V>(rw, kb_off(r, z0 + 1));
-            skb[0][r] = bld_nt<R, V>(rw, kb_off(r, z0));
-        } else {
-            sv[1][r] = v_ld(v_off(r, z0));
-            sv[0][r] = 0.0;
-            skb[1][r] = bld_nt<R, V>(rw, kb_off(r, z0));
-            skb[0][r] = czero<V>();
+    auto kb_ld = [&](int r, int zq) -> V {
+        unsigned off = kBufNone;
+        if (proj && zq >= z0 && zq < z1) {
+            const int2 ri = sRow[(zq - z0) * TY + row0 + r];
+            const unsigned d = (unsigned)x - (unsigned)(ri.x & 0xffff);
+            if (valid[r] && d <= (unsigned)ri.x >> 16)
+                off = (unsigned)(ri.y + x) * (unsigned)sizeof(V);
         }
+        return bld_nt<R, V>(rw, off, 0);
+    };
+    // own values and halo of one plane into an LDS buffer
+    auto put_own = [&](V *buf) {
+        const int rs = fresh(RS);
+#pragma unroll
+        for (int r = 0; r < RPT; ++r)
+            if (valid[r])
+                buf[own + r * rs] = c[r];
+        if (xcopy && (x < kHalf || x >= nx - kHalf)) {
+            // wrap by +1 (phase 41) to the right of the row, by -1 (39) to
+            // its left
+            const int w = fresh(nx);
+            const bool left = x < kHalf;
+            const V ph = sPh[left ? 41 : 39];
+            V *d = buf + own + (left ? w : -w);
+#pragma unroll
+            for (int r = 0; r < RPT; ++r)
+                if (valid[r])
+                    d[r * rs] = cmulf(c[r], ph);
+        }
+    };
+    auto put_halo = [&](V *buf, int i, V v) {
+        const int o = fresh(0);
+        if (hof[i] != kBufNone) {
+            const int pid = hpk[i] >> 20;
+            if (pid != 40)
+                v = cmulf(v, sPh[pid + o]);
+            buf[(hpk[i] & 0xfffff) + o] = v;
+        }
+    };
+
+    // ---- plane z0: halo, potential, KB term; with two planes of lead also
+    // plane z0 + 1 ----
+    constexpr int PF = !SC || RPT == 1 ? 2 : 1;
+    constexpr int NS = SC ? PF : 2 * PF;   // sets of potential and KB term
+    // plane of the own rows loaded for plane zq of the column (-1: none)
+    auto ahead = [&](int zq) -> int {
+        return zq < z1 + (CUR ? 0 : 4) ? wrap_z(zq) : -1;
+    };
+    V shv[PF][HM], snq[PF][RPT], skb[NS][RPT];
+    VV sv[NS][RPT];
+    {
+        V hv0[HM];
+#pragma unroll
+        for (int i = 0; i < HM; ++i)
+            hv0[i] = halo_ld(i, z0);
+        __syncthreads();   // zeroed buffers, phase tables, hull rows ready
+        if constexpr (!SC) {
+#pragma unroll
+            for (int r = 0; r < RPT; ++r) {
+                sv[0][r] = v_ld(r, z0);
+                skb[0][r] = kb_ld(r, z0);
+#pragma unroll
+                for (int m = 0; m <= 8; ++m)
+                    q[r][m] = own_fix(q[r][m], z0 - 4 + m);
+                c[r] = q[r][4];
+            }
+        }
+        if constexpr (PF == 2) {
+#pragma unroll
+            for (int i = 0; i < HM; ++i)
+                shv[1][i] = halo_ld(i, z0 + 1);
+#pragma unroll
+            for (int r = 0; r < RPT; ++r) {
+                snq[1][r] = own_ld(r, SC ? wrap_z(z0 + 1) : ahead(z0 + 5));
+                if constexpr (SC) {   // no output is complete before z0 + 4
+                    sv[1][r] = 0;
+                    skb[1][r] = czero<V>();
+                } else {
+                    sv[1][r] = v_ld(r, z0 + 1);
+                    skb[1][r] = kb_ld(r, z0 + 1);
+                }
+            }
+        }
+        put_own(buf0);
+#pragma unroll
+        for (int i = 0; i < HM; ++i)
+            put_halo(buf0, i, hv0[i]);
+        if constexpr (SC)
+#pragma unroll
+            for (int r = 0; r < RPT; ++r)
+#pragma unroll
+                for (int m = 1; m <= 4; ++m)
+                    p[r][4 - m] = own_fix(p[r][4 - m], z0 - m);
     }
 
+    // ---- coefficients, uniform over the workgroup.  FP64: CL[axis][m] =
+    // -c_m / (2 h^2) (from the host, with c0 the centre), CG[axis][m] =
+    // A d_m / h (or d_m / h in mode kCurrent).  FP32: the weights and, apart,
+    // 1 / h^2 and A / h ----
+    R CL[3][5], CG[3][5];
     R LC[5], GD[5];
 #pragma unroll
-    for (int m = 0; m < 5; ++m) {
-        LC[m] = (R)kLap[m];
-        GD[m] = (R)kGrad[m];
+    for (int m = 1; m <= 4; ++m) {
+        if constexpr (SC) {
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) {
+                CL[ax][m] = a.cl[ax][m - 1];
+                const double A =
+                    ax == 0 ? Avec.x : (ax == 1 ? Avec.y : Avec.z);
+                CG[ax][m] = uni((R)((CUR ? 1.0 : A) * a.cg[ax][m - 1]));
+            }
+        } else {
+            LC[m] = (R)kLap[m];
+            GD[m] = (R)kGrad[m];
+        }
     }
+    const R c0 = SC ? (R)a.c0 : (R)0;
     const R ih2x = (R)(1.0 / (a.geo.h[0] * a.geo.h[0]));
     const R ih2y = (R)(1.0 / (a.geo.h[1] * a.geo.h[1]));
     const R ih2z = (R)(1.0 / (a.geo.h[2] * a.geo.h[2]));
-    const R c0sum = LC[0] * (ih2x + ih2y + ih2z);
+    const R c0sum = (R)kLap[0] * (ih2x + ih2y + ih2z);
     const R Ax = (R)(Avec.x / a.geo.h[0]), Ay = (R)(Avec.y / a.geo.h[1]),
             Az = (R)(Avec.z / a.geo.h[2]);
-    const V cs = cmk<V>(a.cre, a.cim);
+    const R sc = uni((R)a.cim);
     const double w_occ = FIN ? gp(a.wocc)[sg] : 0.0;
     double nrm = 0.0;
     double jc[3] = {0.0, 0.0, 0.0};   // kCurrent: Im(conj psi [H, r_a] psi)
-
-    // one plane; PH = (z - z0) & 1 selects the LDS buffer holding plane z
-    // and, with two register sets (PF = 2), the set the loads of plane
-    // z+2 go to (the other set holds plane z+1).  With one set (PF = 1)
-    // the loads of plane z+1 are issued at the start of plane z and used
-    // at its end, so no load is in flight across planes.
-    constexpr int PF = KS_HPSI_PF;
-    static_assert(PF == 1 || PF == 2, "pipeline depth of one or two planes");
-    auto plane_step = [&](auto Pc, const int z) {
-        constexpr int PH = decltype(Pc)::value;
-        constexpr int LS = PF == 2 ? PH : 0;       // set loaded now
-        constexpr int CS = PF == 2 ? 1 - PH : 0;   // set used at the end
-        V *cur = PH == 0 ? buf0 : buf1;
-        V *nxt = PH == 0 ? buf1 : buf0;
-        // potential and KB term of plane z (loaded two planes ago into
-        // this set) before the set is refilled
-        double vc[RPT];
-        V kbc[RPT];
+    // pending outputs of planes z-1 .. z-4 (slots as p)
+    V o[RPT][4];
 #pragma unroll
-        for (int r = 0; r < RPT; ++r) {
-            vc[r] = sv[PF == 2 ? PH : 1][r];
-            kbc[r] = skb[PF == 2 ? PH : 1][r];
-        }
-        // keep the refills below the reads of the set's previous values
-        // (no load may be scheduled above them: its register would then
-        // still hold a live value and need a copy, i.e. a wait)
-        __builtin_amdgcn_sched_barrier(0);
-        // the final pass's other inputs at plane z, then plane z+2 of
-        // every stream (in flight during this plane and the next)
+    for (int r = 0; r < RPT; ++r)
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+            o[r][m] = czero<V>();
+
+    auto plane_step = [&](auto Pc, const int z) {
+        constexpr int PH = decltype(Pc)::value;    // (z - z0) % 4
+        constexpr int LS = PF == 2 ? PH & 1 : 0;   // set loaded now
+        constexpr int CS = PF == 2 ? 1 - (PH & 1) : 0;   // set of plane z+1
+        const V *cur = (PH & 1) == 0 ? buf0 : buf1;
+        V *nxt = (PH & 1) == 0 ? buf1 : buf0;
+        constexpr int LV = SC ? LS : (PH + PF) & (NS - 1);
+        constexpr int UV = SC ? CS : PH & (NS - 1);
+        const int zo = SC ? z - 4 : z;             // output plane completed
+        const bool emit = zo >= z0;
+        const int so = (emit ? zo : 0) * P;
+        // the final pass's other inputs at plane zo, then plane z + PF
         double2 fb[RPT];
         TT f1[RPT], f2[RPT];
 #pragma unroll
         for (int r = 0; r < RPT; ++r) {
             if constexpr (FIN) {
-                const unsigned gi = (unsigned)(z * P + po[r]);
-                fb[r] = bld_raw_nt<double2>(rbase,
-                                            act[r] ? gi * 16u : kOOB);
+                const unsigned ot = off_of(r, sizeof(TT));
+                fb[r] = bld_raw_nt<double2>(buf_any(a.base + sN, emit),
+                                            p16[r], so * 16);
                 f1[r] = bld_raw_nt<TT>(
-                    rt1, act[r] ? gi * (unsigned)sizeof(TT) : kOOB);
+                    buf_any(reinterpret_cast<const TT *>(a.t1) + sN, emit),
+                    ot, so * (int)sizeof(TT));
                 f2[r] = bld_raw_nt<TT>(
-                    rt2, act[r] ? gi * (unsigned)sizeof(TT) : kOOB);
+                    buf_any(reinterpret_cast<const TT *>(a.t2) + sN, emit),
+                    ot, so * (int)sizeof(TT));
             }
         }
 #pragma unroll
         for (int i = 0; i < HM; ++i)
-            shv[LS][i] = bld<R, InT>(rin, halo_off(i, z + PF));
+            shv[LS][i] = halo_ld(i, z + PF);
+        const int zn = ahead(SC ? z + PF : z + 4 + PF);
+        // FP64 uses them at the end of the step that completes their plane
+        const int zv = SC ? zo + PF - 1 : z + PF;
 #pragma unroll
         for (int r = 0; r < RPT; ++r) {
-            snq[LS][r] = bld<R, InT>(rin, col_off(r, z + kHalf + PF));
-            sv[LS][r] = v_ld(v_off(r, z + PF));
-            skb[LS][r] = bld_nt<R, V>(rw, kb_off(r, z + PF));
+            snq[LS][r] = own_ld(r, zn);
+            if constexpr (!CUR) {
+                sv[LV][r] = v_ld(r, zv);
+                skb[LV][r] = kb_ld(r, zv);
+            }
         }
-        __syncthreads();
+        // FP64: plane z's share of the pending outputs, their z+m taps
+        V done[RPT], cdone[RPT];
+        if constexpr (SC)
 #pragma unroll
-        for (int r = 0; r < RPT; ++r) {
-            const V c = q[r][kHalf];
-            const V *rp = cur + own[r];
-            V hp = czero<V>();
-            if (act[r]) {
-                V sx = czero<V>(), sy = czero<V>(), sz = czero<V>();
-                V gx = czero<V>(), gy = czero<V>(), gz = czero<V>();
-                V ux = czero<V>(), uy = czero<V>(), uz = czero<V>();
+            for (int r = 0; r < RPT; ++r) {
 #pragma unroll
-                for (int m = 1; m <= kHalf; ++m) {
-                    const V xp = rp[m], xn = rp[-m];
-                    const V yp = rp[m * RS], yn = rp[-m * RS];
-                    const V zp = q[r][kHalf + m], zn = q[r][kHalf - m];
-                    sx = cadd(sx, cscale(cadd(xp, xn), LC[m]));
-                    sy = cadd(sy, cscale(cadd(yp, yn), LC[m]));
-                    sz = cadd(sz, cscale(cadd(zp, zn), LC[m]));
+                for (int m = 1; m <= 4; ++m) {
+                    V &t = o[r][(PH + 4 - m) & 3];
+                    t = cfma(CL[2][m], c[r], t);
                     if constexpr (GRAD) {
-                        gx = cadd(gx, cscale(csub(xp, xn), GD[m]));
-                        gy = cadd(gy, cscale(csub(yp, yn), GD[m]));
-                        gz = cadd(gz, cscale(csub(zp, zn), GD[m]));
-                    }
-                    if constexpr (MODE == kCurrent) {
-                        // taps of the gauge term weighted by their
-                        // displacement: sum m d_m (psi_+m + psi_-m)
-                        const R wm = (R)m * GD[m];
-                        ux = cadd(ux, cscale(cadd(xp, xn), wm));
-                        uy = cadd(uy, cscale(cadd(yp, yn), wm));
-                        uz = cadd(uz, cscale(cadd(zp, zn), wm));
+                        t.x = rfma(CG[2][m], c[r].y, t.x);
+                        t.y = rfma(-CG[2][m], c[r].x, t.y);
                     }
                 }
-                if constexpr (MODE == kCurrent) {
-                    // [H, r_a] psi = -grad_a psi - i A_a sum m d_m (psi_+ +
-                    // psi_-): the kinetic taps -c_m/(2h^2) at displacement
-                    // m h give -d_m/h (m c_m = 2 d_m for these weights)
-                    const V gg[3] = {gx, gy, gz}, uu[3] = {ux, uy, uz};
+                done[r] = o[r][PH];
+                cdone[r] = p[r][PH];
+            }
+        if (z < z1) {
+            __syncthreads();
+            const int rs = fresh(RS);
+            const V *rp = cur + own;
+            V yv[RPT + 8];        // y neighbours of all rows: rows -4 ..
 #pragma unroll
-                    for (int ax = 0; ax < 3; ++ax) {
-                        const double ih = 1.0 / a.geo.h[ax];
-                        const double A = ax == 0 ? Avec.x
-                                                 : (ax == 1 ? Avec.y : Avec.z);
-                        const double tx = -gg[ax].x * ih + A * uu[ax].y;
-                        const double ty = -gg[ax].y * ih - A * uu[ax].x;
-                        jc[ax] += c.x * ty - c.y * tx;
+            for (int j = 0; j <= 8; ++j)
+                yv[j] = j == 4 ? c[0] : rp[(j - 4) * rs];
+#pragma unroll
+            for (int r = 0; r < RPT; ++r) {
+                if (r > 0 && r >= rpt)
+                    continue;
+                if (r > 0)
+                    yv[r + 8] = rp[(r + 4) * rs];
+                const V *rx = rp + r * rs;
+                const V cc = c[r];
+                V sx = czero<V>(), sy = czero<V>(), sz = czero<V>();
+                V g = czero<V>();
+                if constexpr (CUR) {
+                    // [H, r_a] has the taps -+d_m / h_a - i A_a m d_m at
+                    // displacement +-m h_a (the kinetic taps -c_m / (2 h^2)
+                    // times m h, m c_m = 2 d_m for these weights); both ends
+                    // of a pair of points give the same Im(conj psi [H, r_a]
+                    // psi), so the lower neighbours count twice and the
+                    // upper ones are not read
+                    auto axis = [&](auto Ax, double A, auto nb) {
+                        constexpr int ax = decltype(Ax)::value;
+                        V G = czero<V>(), U = czero<V>();
+#pragma unroll
+                        for (int m = 4; m >= 1; --m)
+                            G = cfma(CG[ax][m], nb(m), G);
+                        jc[ax] += act[r] ? 2.0 * (cc.x * G.y - cc.y * G.x)
+                                         : 0.0;
+                        if (A != 0.0) {
+#pragma unroll
+                            for (int m = 4; m >= 1; --m)
+                                U = cfma(m * CG[ax][m], nb(m), U);
+                            jc[ax] -= act[r] ? 2.0 * A * a.geo.h[ax] *
+                                                   (cc.x * U.x + cc.y * U.y)
+                                             : 0.0;
+                        }
+                    };
+                    axis(std::integral_constant<int, 0>{}, Avec.x,
+                         [&](int m) { return rx[-m]; });
+                    axis(std::integral_constant<int, 1>{}, Avec.y,
+                         [&](int m) { return rx[-m * rs]; });
+                    axis(std::integral_constant<int, 2>{}, Avec.z,
+                         [&](int m) { return p[r][(PH + 4 - m) & 3]; });
+                    continue;
+                }
+                if constexpr (!SC) {
+                    // the FP32 sums keep their order, and so their bits:
+                    // pairs of taps, the weights apart from 1 / h^2
+                    V gx = czero<V>(), gy = czero<V>(), gz = czero<V>();
+#pragma unroll
+                    for (int m = 1; m <= 4; ++m) {
+                        const V xp = rx[m], xn = rx[-m];
+                        const V yp = yv[r + 4 + m], yn = yv[r + 4 - m];
+                        const V zp = q[r][4 + m], zn = q[r][4 - m];
+                        sx = cfma(LC[m], cadd(xp, xn), sx);
+                        sy = cfma(LC[m], cadd(yp, yn), sy);
+                        sz = cfma(LC[m], cadd(zp, zn), sz);
+                        if constexpr (GRAD == 1) {
+                            gx = cfma(GD[m], csub(xp, xn), gx);
+                            gy = cfma(GD[m], csub(yp, yn), gy);
+                        }
+                        if constexpr (GRAD)
+                            gz = cfma(GD[m], csub(zp, zn), gz);
                     }
-                } else {
-                    V lap = cadd(cadd(cscale(sx, ih2x), cscale(sy, ih2y)),
-                                 cscale(sz, ih2z));
-                    lap = cadd(lap, cscale(c, c0sum));
-                    const R vv = (R)(vc[r] + Avec.w);
-                    hp = cadd(cscale(lap, (R)-0.5), cscale(c, vv));
+                    V lap = cfma(ih2x, sx, cscale(sy, ih2y));
+                    lap = cfma(ih2z, sz, lap);
+                    lap = cfma(c0sum, cc, lap);
+                    const R vv = (R)((double)sv[UV][r] + Avec.w);
+                    V hp = cfma(vv, cc, cscale(lap, (R)-0.5));
                     if constexpr (GRAD) {
                         // -i A.grad
-                        const V gr = cadd(cadd(cscale(gx, Ax),
-                                               cscale(gy, Ay)),
-                                          cscale(gz, Az));
+                        V gr = cfma(Ax, gx, cscale(gy, Ay));
+                        gr = cfma(Az, gz, gr);
                         hp.x += gr.y;
                         hp.y -= gr.x;
                     }
-                    hp = cadd(hp, kbc[r]);
+                    done[r] = cadd(hp, skb[UV][r]);
+                    cdone[r] = cc;
+                    continue;
                 }
+#pragma unroll
+                for (int m = 4; m >= 1; --m) {
+                    const V xn = rx[-m], xp = rx[m];
+                    const V yn = yv[r + 4 - m], yp = yv[r + 4 + m];
+                    const V zn = p[r][(PH + 4 - m) & 3];
+                    sx = cfma(CL[0][m], xn, sx);
+                    sy = cfma(CL[1][m], yn, sy);
+                    sz = cfma(CL[2][m], zn, sz);
+                    sx = cfma(CL[0][m], xp, sx);
+                    sy = cfma(CL[1][m], yp, sy);
+                    if constexpr (GRAD == 1) {
+                        g = cfma(CG[0][m], xp, g);
+                        g = cfma(-CG[0][m], xn, g);
+                        g = cfma(CG[1][m], yp, g);
+                        g = cfma(-CG[1][m], yn, g);
+                    }
+                }
+                V h = cadd(cadd(sx, sy), sz);
+                h = cfma(c0, cc, h);
+                if constexpr (GRAD) {
+                    // -i A.grad
+#pragma unroll
+                    for (int m = 4; m >= 1; --m)
+                        g = cfma(-CG[2][m], p[r][(PH + 4 - m) & 3], g);
+                    h.x += g.y;
+                    h.y -= g.x;
+                }
+                o[r][PH] = h;
             }
-            if constexpr (MODE != kCurrent) {
-                const unsigned gi = (unsigned)(z * P + po[r]);
+        }
+        // output of plane zo
+        if constexpr (!CUR) {
+#pragma unroll
+            for (int r = 0; r < RPT; ++r) {
+                const BufRes rout = buf_any(out + so, emit);
+                const unsigned off = off_of(r, sizeof(OutT));
+                // FP64: potential and KB term of the finished point
+                V hp = done[r];
+                if constexpr (SC)
+                    hp = cadd(cfma((R)(sv[UV][r] + Avec.w), cdone[r], hp),
+                              skb[UV][r]);
                 if constexpr (MODE == kApply) {
-                    bst<double2>(rout, act[r] ? gi * 16u : kOOB,
-                                 (double)hp.x, (double)hp.y);
+                    bst<double2>(rout, off, (double)hp.x, (double)hp.y);
                 } else if constexpr (MODE == kTerm) {
-                    const V t = cmul(cs, hp);
-                    bst<TT>(rout, act[r] ? gi * (unsigned)sizeof(TT) : kOOB,
-                            t.x, t.y);
+                    bst<TT>(rout, off, -sc * hp.y, sc * hp.x);
                 } else {
-                    const V t4 = cmul(cs, hp);
+                    const V t4 = cmk<V>(-sc * hp.y, sc * hp.x);
+                    const V t3 = cdone[r];
                     const double2 bb = fb[r];
                     const TT u1 = f1[r], u2 = f2[r];
                     const double re = bb.x + (double)u1.x + (double)u2.x +
-                                      (double)c.x + (double)t4.x;
+                                      (double)t3.x + (double)t4.x;
                     const double im = bb.y + (double)u1.y + (double)u2.y +
-                                      (double)c.y + (double)t4.y;
-                    bst<double2>(rout, act[r] ? gi * 16u : kOOB, re, im);
+                                      (double)t3.y + (double)t4.y;
+                    bst<double2>(rout, off, re, im);
                     double part;
                     if constexpr (MODE == kFinalPred) {
                         const double pr = bb.x + 2.0 * u1.x + 4.0 * u2.x +
-                                          8.0 * c.x + 16.0 * (double)t4.x;
+                                          8.0 * t3.x + 16.0 * (double)t4.x;
                         const double pi = bb.y + 2.0 * u1.y + 4.0 * u2.y +
-                                          8.0 * c.y + 16.0 * (double)t4.y;
+                                          8.0 * t3.y + 16.0 * (double)t4.y;
                         part = w_occ * (pr * pr + pi * pi);
                     } else {
                         const double sq = re * re + im * im;
                         part = w_occ * sq;
-                        if (act[r])
+                        if (act[r] && emit)
                             nrm += sq;
                     }
-                    bst_d(rnp, act[r] ? gi * 8u : kOOB, part);
+                    bst_d(buf_any(a.npart + sN + so, emit && a.npart),
+                          p8[r], part);
                 }
             }
         }
-        // plane z+1 into the other buffer (free: its last readers passed
-        // this plane's barrier): own values from the columns, the halo from
-        // the other register set (loaded during the previous plane)
-        if (z + 1 < z1) {
-#pragma unroll
-            for (int r = 0; r < RPT; ++r)
-                if (act[r])
-                    nxt[own[r]] = q[r][kHalf + 1];
-#pragma unroll
-            for (int i = 0; i < HM; ++i)
-                if (hoff[i] >= 0)
-                    nxt[hpk[i] & 0xfffff] = halo_fix(i, shv[CS][i]);
-        }
+        // plane z + 1 into the other buffer (free: its last readers passed
+        // this plane's barrier)
 #pragma unroll
         for (int r = 0; r < RPT; ++r) {
+            if constexpr (SC) {
+                p[r][PH] = c[r];
+                c[r] = z + 1 < zend ? own_fix(snq[CS][r], z + 1) : c[r];
+            } else {
 #pragma unroll
-            for (int m = 0; m < 2 * kHalf; ++m)
-                q[r][m] = q[r][m + 1];
-            q[r][2 * kHalf] = col_fix(snq[CS][r], z + kHalf + 1);
-            if constexpr (PF == 1) {
-                sv[1][r] = sv[0][r];     // potential and KB term of z + 1
-                skb[1][r] = skb[0][r];
+                for (int m = 0; m < 8; ++m)
+                    q[r][m] = q[r][m + 1];
+                q[r][8] = z + 5 < z1 + 4 ? own_fix(snq[CS][r], z + 5)
+                                         : snq[CS][r];
+                c[r] = q[r][4];
             }
         }
+        if (z + 1 < z1) {
+            put_own(nxt);
+#pragma unroll
+            for (int i = 0; i < HM; ++i)
+                put_halo(nxt, i, shv[CS][i]);
+        }
     };
-    int z = z0;
-    for (; z + 1 < z1; z += 2) {
+    // planes z1 .. z1 + 3 only complete the last outputs
+    for (int z = z0; z < zend; z += 4) {
         plane_step(std::integral_constant<int, 0>{}, z);
-        plane_step(std::integral_constant<int, 1>{}, z + 1);
+        if (z + 1 < zend)
+            plane_step(std::integral_constant<int, 1>{}, z + 1);
+        if (z + 2 < zend)
+            plane_step(std::integral_constant<int, 2>{}, z + 2);
+        if (z + 3 < zend)
+            plane_step(std::integral_constant<int, 3>{}, z + 3);
     }
-    if (z < z1)
-        plane_step(std::integral_constant<int, 0>{}, z);
     if constexpr (MODE == kFinal) {
         if (!a.normpart)
             return;
@@ -928,7 +1150,7 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
         if (tid == 0)
             gp(a.normpart)[(size_t)sl * ntiles + tile] = vals[0];
     }
-    if constexpr (MODE == kCurrent) {
+    if constexpr (CUR) {
         __syncthreads();
         block_sum<double, 3>(jc, reinterpret_cast<double *>(smem_raw));
         if (tid == 0)

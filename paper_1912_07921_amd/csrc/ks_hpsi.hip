@@ -2,32 +2,14 @@
 #ifndef KS_HPSI_PART
 #define KS_HPSI_PART 0
 #endif
-// Planes the H.psi kernel's loads run ahead: the FP64 kernels (part 0)
-// keep one register set (fewer registers; measured faster at 64^3, 48^3
-// and 128^3), the mixed ones two alternating sets.
-#ifndef KS_HPSI_PF
-#define KS_HPSI_PF (KS_HPSI_PART == 0 ? 1 : 2)
-#endif
-
 #include "ks_device.h"
 
 #include <algorithm>
 
 namespace ks {
 
-// Occupancy hint (waves per SIMD the register allocation must allow); 0
-// leaves the choice to the compiler.
-#ifndef KS_HPSI_MIN_WAVES
-#define KS_HPSI_MIN_WAVES 0
-#endif
-#if KS_HPSI_MIN_WAVES > 0
-#define KS_HPSI_ATTR __attribute__((amdgpu_waves_per_eu(KS_HPSI_MIN_WAVES)))
-#else
-#define KS_HPSI_ATTR
-#endif
-
-template <class R, class InT, class TT, int MODE, bool GRAD, int HM, int RPT>
-__global__ __launch_bounds__(512) KS_HPSI_ATTR void k_hpsi(HArgs a)
+template <class R, class InT, class TT, int MODE, int GRAD, int HM, int RPT>
+__global__ __launch_bounds__(512) void k_hpsi(HArgs a)
 {
     hpsi_item<R, InT, TT, MODE, GRAD, HM, RPT>(
         a, xcd_remap(blockIdx.x, gridDim.x),
@@ -46,11 +28,7 @@ int hpsi_threads(int nx, int TY, int rpt)
 
 int hpsi_halo_per_thread(const Geo &g, int TY, int nthr)
 {
-    // dynamic halo entries (in-grid rows, and wrapped columns on a
-    // periodic x axis) of a full tile
-    const int dyn = 2 * kHalf * g.nx + (g.per[0] ? 2 * kHalf * (TY + 2 * kHalf)
-                                                  : 0);
-    const int hm = (dyn + nthr - 1) / nthr;
+    const int hm = (halo_loads(g, TY) + nthr - 1) / nthr;
     return hm <= 2 ? 2 : (hm <= 4 ? 4 : (hm <= 8 ? 8 : 16));
 }
 
@@ -58,12 +36,12 @@ size_t hpsi_lds_bytes(int nx, int TY, int zchunk, bool mixed)
 {
     const size_t v = mixed ? 8 : 16;
     return 2 * (size_t)(TY + 2 * kHalf) * (nx + 2 * kHalf) * v + 90 * v +
-           (size_t)zchunk * TY * sizeof(int4);
+           (size_t)zchunk * TY * sizeof(int2);
 }
 
 #endif
 
-template <class R, class InT, class TT, int MODE, bool GRAD>
+template <class R, class InT, class TT, int MODE, int GRAD>
 static hipError_t go_hpsi2(const HArgs &a, int ns, hipStream_t st)
 {
     const int nthr = hpsi_threads(a.geo.nx, a.TY, a.rpt);
@@ -107,9 +85,11 @@ static hipError_t go_hpsi2(const HArgs &a, int ns, hipStream_t st)
 template <class R, class InT, class TT, int MODE>
 static hipError_t go_hpsi(const HArgs &a, int ns, hipStream_t st)
 {
-    const bool grad = (a.A[0] != 0.0) || (a.A[1] != 0.0) || (a.A[2] != 0.0);
-    return grad ? go_hpsi2<R, InT, TT, MODE, true>(a, ns, st)
-                : go_hpsi2<R, InT, TT, MODE, false>(a, ns, st);
+    if (a.A[0] != 0.0 || a.A[1] != 0.0)
+        return go_hpsi2<R, InT, TT, MODE, 1>(a, ns, st);
+    // A along z (a laser polarised along z): a third of the gradient's taps
+    return a.A[2] != 0.0 ? go_hpsi2<R, InT, TT, MODE, 2>(a, ns, st)
+                         : go_hpsi2<R, InT, TT, MODE, 0>(a, ns, st);
 }
 
 // The file is compiled twice: KS_HPSI_PART 0 holds the FP64 kernels and the
@@ -148,19 +128,19 @@ hipError_t launch_hpsi_current(const HArgs &a, int ns, hipStream_t st)
     using D2 = double2;
     switch (hpsi_halo_per_thread(a.geo, a.TY, nthr)) {
     case 2:
-        hipLaunchKernelGGL((k_hpsi<double, D2, D2, kCurrent, true, 2, 1>),
+        hipLaunchKernelGGL((k_hpsi<double, D2, D2, kCurrent, 1, 2, 1>),
                            grid, dim3(nthr), lds, st, a);
         break;
     case 4:
-        hipLaunchKernelGGL((k_hpsi<double, D2, D2, kCurrent, true, 4, 1>),
+        hipLaunchKernelGGL((k_hpsi<double, D2, D2, kCurrent, 1, 4, 1>),
                            grid, dim3(nthr), lds, st, a);
         break;
     case 8:
-        hipLaunchKernelGGL((k_hpsi<double, D2, D2, kCurrent, true, 8, 1>),
+        hipLaunchKernelGGL((k_hpsi<double, D2, D2, kCurrent, 1, 8, 1>),
                            grid, dim3(nthr), lds, st, a);
         break;
     default:
-        hipLaunchKernelGGL((k_hpsi<double, D2, D2, kCurrent, true, 16, 1>),
+        hipLaunchKernelGGL((k_hpsi<double, D2, D2, kCurrent, 1, 16, 1>),
                            grid, dim3(nthr), lds, st, a);
         break;
     }

@@ -97,7 +97,10 @@ struct HArgs {
     const float *v32 = nullptr;    // its FP32 copy (read by the FP32 kernels)
     double a2half = 0.0;           // |A|^2 / 2
     double A[3] = {0.0, 0.0, 0.0};
-    double cre = 1.0, cim = 0.0;   // complex scale of H.in
+    double cim = 0.0;              // scale i cim of H.in (kTerm, final modes)
+    // stencil coefficients, m = 1 .. 4 at [m - 1]: cl[axis] = -c_m / (2 h^2)
+    // (FP64 kernels), c0 the centre, cg[axis] = d_m / h
+    double cl[3][4] = {}, c0 = 0.0, cg[3][4] = {};
     const double2 *kph = nullptr;  // [nk][3] exp(i k_a L_a)
     int nstates = 1;               // states per k-point
     int sg0 = 0;                   // global state index of launch state 0
@@ -156,6 +159,13 @@ int apply_h_scratch(ks_grid *g, const void *d_psi, void *d_hpsi, int k,
 int set_error(int code, const char *msg);
 
 // Launch shape of the H.psi kernel.
+// Halo values a full tile loads per plane: the in-grid (or wrapped) rows
+// and, on a periodic x axis shorter than the halo's 8 columns, those.
+inline int halo_loads(const Geo &g, int TY)
+{
+    return 2 * kHalf * g.nx +
+           (g.per[0] && g.nx < 2 * kHalf ? 2 * kHalf * TY : 0);
+}
 int hpsi_threads(int nx, int TY, int rpt);
 int hpsi_halo_per_thread(const Geo &g, int TY, int nthr);
 size_t hpsi_lds_bytes(int nx, int TY, int zchunk, bool mixed);
