@@ -445,10 +445,10 @@ struct Shape {
 // us) and a time per plane that grows with the wavefronts resident on its CU;
 // the launch takes that for every round of workgroups over the 256 CUs.  A
 // chunk of zc planes marches zc + 4 (the last four only complete outputs).
-// The constants are fits to one pass on MI355X (us per plane at 3 / 5 / 8
-// resident wavefronts: FP64 0.6 / 0.8 / 1.05 with one row per thread, - /
-// 1.35 / 1.9 with two; FP32 0.58 / 0.68 / 0.8 and 1.1 / 1.1 / 1.25), the
-// halo term the difference of 8 and 16-row tiles at 64^3.  Few states and
+// The constants are fits to one pass on MI355X (us per plane at 3 / 5 / 8 /
+// 12 resident wavefronts: FP64 0.6 / 0.8 / 1.05 / 1.6 with one row per thread,
+// - / 1.35 / 1.9 / - with two; FP32 0.58 / 0.68 / 0.8 / - and 1.1 / 1.1 / 1.25
+// / -), the halo term the difference of 8 and 16-row tiles at 64^3.  Few states and
 // small grids thus get short chunks of low tiles (24^3 x 4 states, 4 -> 192
 // workgroups: 40 -> 6 us per pass), large ones tall tiles of the whole axis.
 // rpt_only > 0 restricts the rows per thread (the current's kernel has one).
@@ -462,11 +462,22 @@ Shape pick_shape(const ks_grid *g, int ns, int rpt_only = 0)
     for (int rpt = 1; rpt <= 2; ++rpt) {
         if (rpt_only > 0 && rpt != rpt_only)
             continue;
-        // time per plane a + b * resident wavefronts
-        const double pa = mx ? (rpt == 1 ? 0.45 : 0.85)
-                             : (rpt == 1 ? 0.42 : 0.50);
-        const double pb = mx ? (rpt == 1 ? 0.052 : 0.05)
-                             : (rpt == 1 ? 0.08 : 0.17);
+        // time per plane a + b w + c w^2 at w resident wavefronts (two rows
+        // per thread on a periodic grid: 0.2 us more for the wrapped columns)
+        const bool per = G.per[0] || G.per[1] || G.per[2];
+        double pa = 0.42, pb = 0.05, pc = 0.004;
+        if (rpt_only > 0) {
+            pb = 0.08;
+            pc = 0.0;
+        } else if (rpt == 2) {
+            pa = mx ? 0.85 : (per ? 0.70 : 0.50);
+            pb = mx ? 0.05 : 0.17;
+            pc = 0.0;
+        } else if (mx) {
+            pa = 0.45;
+            pb = 0.052;
+            pc = 0.0;
+        }
         for (int nt = 1, last = 0; nt <= G.ny; ++nt) {
             const int TY = (G.ny + nt - 1) / nt;
             if (TY == last || TY < rpt || !tile_ok(g, TY, rpt))
@@ -491,14 +502,17 @@ Shape pick_shape(const ks_grid *g, int ns, int rpt_only = 0)
                 const long nwg = (long)ntile * ((G.nz + zc - 1) / zc) * ns;
                 // wavefronts a CU holds (registers): four or three per SIMD
                 // with one row per thread (FP32, FP64), two with two
-                const int room = rpt == 2 ? 8 : (mx ? 16 : 12);
+                // (and the current's)
+                const int room =
+                    rpt == 2 || rpt_only > 0 ? 8 : (mx ? 16 : 12);
                 const int fit = std::max(
                     1, std::min(room / std::max(1, w),
                                 (int)(kLdsBudget / lds)));
                 const long per_cu = std::min<long>(
                     fit, (nwg + kCUs - 1) / kCUs);
                 const long rounds = (nwg + kCUs * fit - 1) / (kCUs * fit);
-                const double plane = (pa + pb * (double)(per_cu * w)) * halo *
+                const double wr = (double)(per_cu * w);
+                const double plane = (pa + pb * wr + pc * wr * wr) * halo *
                                      (spills ? 1.3 : 1.0);
                 const double t = rounds * (2.5 + (zc + 4) * plane);
                 if (t < t_best) {

@@ -1342,6 +1342,115 @@ __device__ __forceinline__ void gather_finalize_item(const GArgs &a,
     gst(reinterpret_cast<V *>(a.D) + i, cmk<V>(e * re, e * im));
 }
 
+// Both stages for one atom and one state in one workgroup, for launches of
+// few states, which the latency of a launch and of its dependent loads bounds:
+// wavefront w takes the chunks w, w + W, .. of the sphere (W
+// wavefronts), the chunk sums meet in LDS and the coefficients are written
+// at once, without partials and a second launch.  The points, the lanes and
+// the chunks are summed in the order of the two stages, so the bits are the
+// same.  smem: W * kSphereRow reduction rows, then nchunk * 2 * kMaxProj sums.
+constexpr int kSphereRow = 2 * kMaxProj * 65;
+
+template <class R, class InT>
+__device__ __forceinline__ void gather_sphere_item(const GArgs &a,
+                                                   const int at, const int sl,
+                                                   R *smem)
+{
+    using V = typename Cplx<R>::T;
+    constexpr int U = kGatherChunk / 64;      // points per lane
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int W = blockDim.x >> 6;
+    R *red = smem + wave * kSphereRow;
+    R *sums = smem + W * kSphereRow;
+    const int np = gp(a.pj.nproj)[at];
+    const int npt = gp(a.pj.npts)[at];
+    const long io = gp(a.pj.ioff)[at];
+    const double4 ap = gld(a.pj.apos + at);
+    const double2 ar = gld(a.pj.arad + at);
+    const int nx = a.geo.nx, ny = a.geo.ny, nz = a.geo.nz;
+    const double Lx = nx * a.geo.h[0], Ly = ny * a.geo.h[1],
+                 Lz = nz * a.geo.h[2];
+    const int nch = (npt + kGatherChunk - 1) / kGatherChunk;
+    const double2 *kph = a.kph + 3 * ((a.sg0 + sl) / a.nstates);
+    const InT *in = reinterpret_cast<const InT *>(a.in) +
+                    (size_t)sl * a.geo.N;
+    for (int ch = wave; ch < nch; ch += W) {
+        const int p0 = ch * kGatherChunk;
+        const int p1 = min(npt, p0 + kGatherChunk);
+        int gi[U], pk[U], code[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int pt = p0 + lane + 64 * u;
+            const bool ok = pt < p1;
+            gi[u] = ok ? gp(a.pj.sidx)[io + pt] : -1;
+            pk[u] = ok ? gp(a.pj.sxyz)[io + pt] : 0;
+            code[u] = ok ? gp(a.pj.sshift)[io + pt] : 0;
+        }
+        V val[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            val[u] = gi[u] >= 0 ? ldc_g<R>(in, gi[u]) : czero<V>();
+        R acc[2 * kMaxProj];
+#pragma unroll
+        for (int j = 0; j < 2 * kMaxProj; ++j)
+            acc[j] = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (gi[u] < 0)
+                continue;
+            const int ix = pk[u] & 0x3ff, iy = (pk[u] >> 10) & 0x3ff,
+                      iz = pk[u] >> 20;
+            const int tx = (int)(signed char)(code[u] & 0xff);
+            const int ty = (int)(signed char)((code[u] >> 8) & 0xff);
+            const int tz = (int)(signed char)((code[u] >> 16) & 0xff);
+            const double dx = axis_coord(nx, a.geo.h[0], a.geo.per[0], ix) +
+                              tx * Lx - ap.x;
+            const double dy = axis_coord(ny, a.geo.h[1], a.geo.per[1], iy) +
+                              ty * Ly - ap.y;
+            const double dz = axis_coord(nz, a.geo.h[2], a.geo.per[2], iz) +
+                              tz * Lz - ap.z;
+            const double r2 = dx * dx + dy * dy + dz * dz;
+            R p[kMaxProj];
+            proj_shape<R>(dx, dy, dz, r2, ar, np, p);
+            V v = val[u];
+            if (code[u])
+                v = cmul(v, shift_phase<V>(kph, code[u]));
+#pragma unroll
+            for (int j = 0; j < kMaxProj; ++j) {
+                acc[2 * j] += p[j] * v.x;
+                acc[2 * j + 1] += p[j] * v.y;
+            }
+        }
+        // the lanes in order, through this wavefront's own LDS rows
+#pragma unroll
+        for (int j = 0; j < 2 * kMaxProj; ++j)
+            red[j * 65 + lane] = acc[j];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (lane < 2 * kMaxProj) {
+            R sum = 0;
+            for (int r = 0; r < 64; ++r)
+                sum += red[lane * 65 + r];
+            sums[ch * 2 * kMaxProj + lane] = sum;
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    const int j = threadIdx.x;
+    if (j < kMaxProj) {
+        R re = 0, im = 0;
+        for (int c = 0; c < nch; ++c) {
+            re += sums[(2 * c) * kMaxProj + 2 * j];
+            im += sums[(2 * c) * kMaxProj + 2 * j + 1];
+        }
+        const R e = j < np ? (R)gp(a.pj.EjN2)[at * kMaxProj + j] : (R)0;
+        gst(reinterpret_cast<V *>(a.D) +
+                ((size_t)sl * a.pj.natoms + at) * kMaxProj + j,
+            cmk<V>(e * re, e * im));
+    }
+}
+
 // V_NL in on the hull: W[s][h] = sum over atoms a whose sphere holds hull
 // point h of sum_j P_j(r) rad(r) D[s][a][j] exp(-i k.T).  A workgroup takes
 // a chunk of 64 hull points (one per lane) and kApplyWaves * SPW states

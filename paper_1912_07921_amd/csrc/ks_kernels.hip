@@ -32,6 +32,18 @@ __global__ __launch_bounds__(256) void k_gather_finalize(GArgs a)
     gather_finalize_item<R>(a, (long)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
+extern __shared__ double smem_proj[];
+
+// (768 threads: three FP64 wavefronts per SIMD without spills)
+constexpr int kSphereWaves = 12;
+
+template <class R, class InT>
+__global__ __launch_bounds__(64 * kSphereWaves) void k_gather_sphere(GArgs a)
+{
+    gather_sphere_item<R, InT>(a, blockIdx.x, blockIdx.y,
+                               reinterpret_cast<R *>(smem_proj));
+}
+
 template <class R, int SPW>
 __global__ __launch_bounds__(kApplyThreads) void k_kbapply(GArgs a)
 {
@@ -422,6 +434,12 @@ int gather_chunk_points() { return kGatherChunk; }
 // (128^3 x 256 states, 64 atoms: 45k workgroups, 0.91 -> 0.83 ms; at 2.5k
 // and 96 workgroups the plain order is 2-10 % faster).
 constexpr long kGatherPlaneOrderMin = 8192;
+// Launches of at most this many (atom, state, chunk) wavefronts give each atom
+// and state one workgroup (k_gather_sphere): 24^3 x 4 states, 72 wavefronts,
+// 8.7 + 4.4 us in two launches -> 8.6; 64^3 x 32, 2304, 13.1 + 5.3 -> 13.6
+// (FP32 13.3 + 5.1 -> 11.5); 48^3 x 64, 3072, 15.6 + 4.6 -> 18.6; 72x60x66 x
+// 40, 3600, 16.1 + 5.3 -> 22.0.
+constexpr long kGatherSphereMax = 3072;
 
 hipError_t launch_gather(bool mixed, bool in_is_f64, const GArgs &a, int ns,
                          hipStream_t st)
@@ -430,6 +448,26 @@ hipError_t launch_gather(bool mixed, bool in_is_f64, const GArgs &a, int ns,
         return hipSuccess;
     GArgs b = a;
     b.ns = ns;
+    // few (atom, state, chunk) wavefronts: one workgroup per atom and state
+    // sums the whole sphere and needs no second launch
+    const int W = std::min(a.nchunk, kSphereWaves);
+    const size_t rs = mixed ? 4 : 8;
+    const size_t lds = rs * ((size_t)W * kSphereRow +
+                             (size_t)a.nchunk * 2 * kMaxProj);
+    if ((long)a.pj.natoms * ns * a.nchunk <= kGatherSphereMax &&
+        lds <= kLdsBudget && ns <= 65535) {
+        dim3 grid(a.pj.natoms, ns), blk(64 * W);
+        if (!mixed)
+            hipLaunchKernelGGL((k_gather_sphere<double, double2>), grid, blk,
+                               lds, st, b);
+        else if (in_is_f64)
+            hipLaunchKernelGGL((k_gather_sphere<float, double2>), grid, blk,
+                               lds, st, b);
+        else
+            hipLaunchKernelGGL((k_gather_sphere<float, float2>), grid, blk,
+                               lds, st, b);
+        return hipGetLastError();
+    }
     const int ngrp = (ns + kGatherStates - 1) / kGatherStates;
     const long nblk = (long)a.pj.ngpairs * ngrp;
     dim3 blk(256);
