@@ -174,6 +174,7 @@ int build_projectors(ks_grid *g, const ks_grid_desc *d)
     const int na = d->natoms;
     g->natoms = na;
     g->pj.natoms = na;
+    g->pj.npmax = 1;
     if (na == 0)
         return KS_OK;
     if (na > 65535)
@@ -200,6 +201,7 @@ int build_projectors(ks_grid *g, const ks_grid_desc *d)
                 return fail(KS_E_UNSUPPORTED,
                             "atom %d: rc must be below half the cell", a);
         nproj[a] = (lmax + 1) * (lmax + 1);
+        g->pj.npmax = std::max(g->pj.npmax, nproj[a]);
         apos[a] = make_double4(X[0], X[1], X[2], rc * rc);
         arad[a] = make_double2(1.0 / (2.0 * sg * sg), 1.0 / (rc * rc));
         // index ranges (unwrapped) of the bounding box of the sphere
@@ -2243,6 +2245,9 @@ BArgs batch_args(const ks_batch *b, int kind, int pass)
     a.off_total = b->off_total[kind];
     a.pass = pass;
     a.hargs = b->d_hargs;
+    a.npmax = 1;
+    for (const JobDev &J : b->hjobs)
+        a.npmax = std::max(a.npmax, J.g.pj.npmax);
     return a;
 }
 

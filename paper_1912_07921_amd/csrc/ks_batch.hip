@@ -86,7 +86,7 @@ __global__ __launch_bounds__(512) void k_hpsi_batch(BArgs b)
     }
 }
 
-template <class R, class InT>
+template <class R, class InT, int NP>
 __global__ __launch_bounds__(256) void k_gather_batch(BArgs b)
 {
     const int total = cp(b.off)[b.njobs];
@@ -100,7 +100,7 @@ __global__ __launch_bounds__(256) void k_gather_batch(BArgs b)
         r /= a.nchunk;
         const int ngrp = (a.ns + kGatherStates - 1) / kGatherStates;
         const int grp = r % ngrp;
-        gather_item<R, InT>(a, r / ngrp, grp, ch);
+        gather_item<R, InT, NP>(a, r / ngrp, grp, ch);
     }
 }
 
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(256) void k_gather_finalize_batch(BArgs b)
     }
 }
 
-template <class R>
+template <class R, int NP>
 __global__ __launch_bounds__(kApplyThreads) void k_kbapply_batch(BArgs b)
 {
     const int total = cp(b.off)[b.njobs];
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(kApplyThreads) void k_kbapply_batch(BArgs b)
         const int jb = find_job(b.off, b.njobs, L);
         const GArgs a = cload<GArgs>(&(cp(b.jobs) + jb)->g);
         const int r = L - cp(b.off)[jb];
-        kbapply_item<R, KS_APPLY_SPW_SMALL>(a, r % a.pj.nhchunk,
+        kbapply_item<R, KS_APPLY_SPW_SMALL, NP>(a, r % a.pj.nhchunk,
                                             r / a.pj.nhchunk);
     }
 }
@@ -263,21 +263,22 @@ hipError_t launch_pass_batch_mixed(const BArgs &b, bool grad, int hm, int rpt,
 #endif
 
 #if KS_HPSI_PART == 0
-hipError_t launch_projectors_batch(bool mixed, const BArgs &bg,
-                                   const BArgs &bf, const BArgs &ba,
-                                   int grid, hipStream_t st)
+template <int NP>
+static hipError_t go_projectors_batch(bool mixed, const BArgs &bg,
+                                      const BArgs &bf, const BArgs &ba,
+                                      int grid, hipStream_t st)
 {
     const int j = (bg.pass - 1) % 4 + 1;
     const bool f64 = !mixed || j == 1;
     if (bg.off_total > 0) {
         if (!mixed)
-            hipLaunchKernelGGL((k_gather_batch<double, double2>), dim3(grid),
+            hipLaunchKernelGGL((k_gather_batch<double, double2, NP>), dim3(grid),
                                dim3(256), 0, st, bg);
         else if (f64)
-            hipLaunchKernelGGL((k_gather_batch<float, double2>), dim3(grid),
+            hipLaunchKernelGGL((k_gather_batch<float, double2, NP>), dim3(grid),
                                dim3(256), 0, st, bg);
         else
-            hipLaunchKernelGGL((k_gather_batch<float, float2>), dim3(grid),
+            hipLaunchKernelGGL((k_gather_batch<float, float2, NP>), dim3(grid),
                                dim3(256), 0, st, bg);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess)
@@ -296,14 +297,23 @@ hipError_t launch_projectors_batch(bool mixed, const BArgs &bg,
     }
     if (ba.off_total > 0) {
         if (!mixed)
-            hipLaunchKernelGGL((k_kbapply_batch<double>), dim3(grid),
+            hipLaunchKernelGGL((k_kbapply_batch<double, NP>), dim3(grid),
                                dim3(kApplyThreads), 0, st, ba);
         else
-            hipLaunchKernelGGL((k_kbapply_batch<float>), dim3(grid),
+            hipLaunchKernelGGL((k_kbapply_batch<float, NP>), dim3(grid),
                                dim3(kApplyThreads), 0, st, ba);
         return hipGetLastError();
     }
     return hipSuccess;
+}
+
+hipError_t launch_projectors_batch(bool mixed, const BArgs &bg,
+                                   const BArgs &bf, const BArgs &ba,
+                                   int grid, hipStream_t st)
+{
+    return bg.npmax <= 4
+               ? go_projectors_batch<4>(mixed, bg, bf, ba, grid, st)
+               : go_projectors_batch<kMaxProj>(mixed, bg, bf, ba, grid, st);
 }
 
 hipError_t launch_step_advance(int *const *steps, int njobs, hipStream_t st)

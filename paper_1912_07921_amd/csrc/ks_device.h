@@ -1167,10 +1167,11 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
 // rad = exp(-r^2 / (2 sigma^2)) (1 - r^2 / rc^2)^2, evaluated here without
 // N_j (which the coefficients carry).
 // ---------------------------------------------------------------------------
-template <class R>
+// NP: the projectors formed, 4 (s and p) where no atom has more, or 9.
+template <class R, int NP = kMaxProj>
 __device__ __forceinline__ void proj_shape(double dx, double dy, double dz,
                                            double r2, double2 ar, int np,
-                                           R p[kMaxProj])
+                                           R p[NP])
 {
     const double wv = 1.0 - r2 * ar.y;
     const R rad = (R)(exp(-r2 * ar.x) * wv * wv);
@@ -1179,12 +1180,14 @@ __device__ __forceinline__ void proj_shape(double dx, double dy, double dz,
     p[1] = rad * X;
     p[2] = rad * Y;
     p[3] = rad * Z;
-    p[4] = rad * X * Y;
-    p[5] = rad * Y * Z;
-    p[6] = rad * Z * X;
-    p[7] = rad * (X * X - Y * Y);
-    p[8] = rad * ((R)3 * Z * Z - (X * X + Y * Y + Z * Z));
-    for (int j = np; j < kMaxProj; ++j)
+    if constexpr (NP > 4) {
+        p[4] = rad * X * Y;
+        p[5] = rad * Y * Z;
+        p[6] = rad * Z * X;
+        p[7] = rad * (X * X - Y * Y);
+        p[8] = rad * ((R)3 * Z * Z - (X * X + Y * Y + Z * Z));
+    }
+    for (int j = np; j < NP; ++j)
         p[j] = 0;
 }
 
@@ -1203,7 +1206,7 @@ constexpr int kGatherChunk = KS_GATHER_CHUNK;
 constexpr int kGatherSPW = KS_GATHER_SPW;   // states per wavefront
 constexpr int kGatherStates = 4 * kGatherSPW;
 
-template <class R, class InT>
+template <class R, class InT, int NP>
 __device__ __forceinline__ void gather_item(const GArgs &a, const int at,
                                             const int grp, const int ch)
 {
@@ -1244,11 +1247,11 @@ __device__ __forceinline__ void gather_item(const GArgs &a, const int at,
                                          (size_t)sl * a.geo.N, gi[u])
                             : czero<V>();
         }
-    R acc[kGatherSPW][2 * kMaxProj];
+    R acc[kGatherSPW][2 * NP];
 #pragma unroll
     for (int q = 0; q < kGatherSPW; ++q)
 #pragma unroll
-        for (int j = 0; j < 2 * kMaxProj; ++j)
+        for (int j = 0; j < 2 * NP; ++j)
             acc[q][j] = 0;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -1266,8 +1269,8 @@ __device__ __forceinline__ void gather_item(const GArgs &a, const int at,
         const double dz = axis_coord(nz, a.geo.h[2], a.geo.per[2], iz) +
                           tz * Lz - ap.z;
         const double r2 = dx * dx + dy * dy + dz * dz;
-        R p[kMaxProj];
-        proj_shape<R>(dx, dy, dz, r2, ar, np, p);
+        R p[NP];
+        proj_shape<R, NP>(dx, dy, dz, r2, ar, np, p);
 #pragma unroll
         for (int q = 0; q < kGatherSPW; ++q) {
             const int sl = s0 + q;
@@ -1279,7 +1282,7 @@ __device__ __forceinline__ void gather_item(const GArgs &a, const int at,
                 v = cmul(v, shift_phase<V>(a.kph + 3 * kk, code[u]));
             }
 #pragma unroll
-            for (int j = 0; j < kMaxProj; ++j) {
+            for (int j = 0; j < NP; ++j) {
                 acc[q][2 * j] += p[j] * v.x;
                 acc[q][2 * j + 1] += p[j] * v.y;
             }
@@ -1288,24 +1291,24 @@ __device__ __forceinline__ void gather_item(const GArgs &a, const int at,
     // sum over the 64 lanes by a transpose through LDS: column c of the
     // workgroup (wave, state, projector, re/im) gets the lanes' values as
     // rows; thread c then adds its column in lane order (deterministic)
-    constexpr int kCols = 4 * kGatherSPW * 2 * kMaxProj;
+    constexpr int kCols = 4 * kGatherSPW * 2 * NP;
     static_assert(kCols <= 256, "one thread of the workgroup per column");
     __shared__ R red[kCols][65];
     __syncthreads();               // the previous item's reads are done
 #pragma unroll
     for (int q = 0; q < kGatherSPW; ++q)
 #pragma unroll
-        for (int j = 0; j < 2 * kMaxProj; ++j)
-            red[(wave * kGatherSPW + q) * 2 * kMaxProj + j][lane] = acc[q][j];
+        for (int j = 0; j < 2 * NP; ++j)
+            red[(wave * kGatherSPW + q) * 2 * NP + j][lane] = acc[q][j];
     __syncthreads();
     const int c = threadIdx.x;
     if (c < kCols) {
         R sum = 0;
         for (int r = 0; r < 64; ++r)
             sum += red[c][r];
-        const int w = c / (2 * kMaxProj * kGatherSPW);
-        const int q = (c / (2 * kMaxProj)) % kGatherSPW;
-        const int jj = c % (2 * kMaxProj);
+        const int w = c / (2 * NP * kGatherSPW);
+        const int q = (c / (2 * NP)) % kGatherSPW;
+        const int jj = c % (2 * NP);
         const int sl = grp * kGatherStates + w * kGatherSPW + q;
         if (sl < a.ns) {
             R *part = reinterpret_cast<R *>(a.Dpart) +
@@ -1331,14 +1334,15 @@ __device__ __forceinline__ void gather_finalize_item(const GArgs &a,
     const int nch = (gp(a.pj.npts)[at] + kGatherChunk - 1) / kGatherChunk;
     const V *part = reinterpret_cast<const V *>(a.Dpart) +
                     (size_t)sa * a.nchunk * kMaxProj + j;
-    R re = 0, im = 0;
-    for (int c = 0; c < nch; ++c) {
-        const V v = gld(part + (size_t)c * kMaxProj);
-        re += v.x;
-        im += v.y;
+    R re = 0, im = 0, e = 0;
+    if (j < gp(a.pj.nproj)[at]) {
+        for (int c = 0; c < nch; ++c) {
+            const V v = gld(part + (size_t)c * kMaxProj);
+            re += v.x;
+            im += v.y;
+        }
+        e = (R)gp(a.pj.EjN2)[at * kMaxProj + j];
     }
-    const R e = (j < gp(a.pj.nproj)[at]) ? (R)gp(a.pj.EjN2)[at * kMaxProj + j]
-                                     : (R)0;
     gst(reinterpret_cast<V *>(a.D) + i, cmk<V>(e * re, e * im));
 }
 
@@ -1348,10 +1352,11 @@ __device__ __forceinline__ void gather_finalize_item(const GArgs &a,
 // wavefronts), the chunk sums meet in LDS and the coefficients are written
 // at once, without partials and a second launch.  The points, the lanes and
 // the chunks are summed in the order of the two stages, so the bits are the
-// same.  smem: W * kSphereRow reduction rows, then nchunk * 2 * kMaxProj sums.
-constexpr int kSphereRow = 2 * kMaxProj * 65;
+// same.  smem: W * sphere_row(NP) reduction rows, then nchunk * 2 * kMaxProj
+// sums.
+__host__ __device__ constexpr int sphere_row(int np) { return 2 * np * 65; }
 
-template <class R, class InT>
+template <class R, class InT, int NP>
 __device__ __forceinline__ void gather_sphere_item(const GArgs &a,
                                                    const int at, const int sl,
                                                    R *smem)
@@ -1361,8 +1366,8 @@ __device__ __forceinline__ void gather_sphere_item(const GArgs &a,
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int W = blockDim.x >> 6;
-    R *red = smem + wave * kSphereRow;
-    R *sums = smem + W * kSphereRow;
+    R *red = smem + wave * sphere_row(NP);
+    R *sums = smem + W * sphere_row(NP);
     const int np = gp(a.pj.nproj)[at];
     const int npt = gp(a.pj.npts)[at];
     const long io = gp(a.pj.ioff)[at];
@@ -1391,9 +1396,9 @@ __device__ __forceinline__ void gather_sphere_item(const GArgs &a,
 #pragma unroll
         for (int u = 0; u < U; ++u)
             val[u] = gi[u] >= 0 ? ldc_g<R>(in, gi[u]) : czero<V>();
-        R acc[2 * kMaxProj];
+        R acc[2 * NP];
 #pragma unroll
-        for (int j = 0; j < 2 * kMaxProj; ++j)
+        for (int j = 0; j < 2 * NP; ++j)
             acc[j] = 0;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -1411,24 +1416,24 @@ __device__ __forceinline__ void gather_sphere_item(const GArgs &a,
             const double dz = axis_coord(nz, a.geo.h[2], a.geo.per[2], iz) +
                               tz * Lz - ap.z;
             const double r2 = dx * dx + dy * dy + dz * dz;
-            R p[kMaxProj];
-            proj_shape<R>(dx, dy, dz, r2, ar, np, p);
+            R p[NP];
+            proj_shape<R, NP>(dx, dy, dz, r2, ar, np, p);
             V v = val[u];
             if (code[u])
                 v = cmul(v, shift_phase<V>(kph, code[u]));
 #pragma unroll
-            for (int j = 0; j < kMaxProj; ++j) {
+            for (int j = 0; j < NP; ++j) {
                 acc[2 * j] += p[j] * v.x;
                 acc[2 * j + 1] += p[j] * v.y;
             }
         }
         // the lanes in order, through this wavefront's own LDS rows
 #pragma unroll
-        for (int j = 0; j < 2 * kMaxProj; ++j)
+        for (int j = 0; j < 2 * NP; ++j)
             red[j * 65 + lane] = acc[j];
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        if (lane < 2 * kMaxProj) {
+        if (lane < 2 * NP) {
             R sum = 0;
             for (int r = 0; r < 64; ++r)
                 sum += red[lane * 65 + r];
@@ -1439,12 +1444,14 @@ __device__ __forceinline__ void gather_sphere_item(const GArgs &a,
     __syncthreads();
     const int j = threadIdx.x;
     if (j < kMaxProj) {
-        R re = 0, im = 0;
-        for (int c = 0; c < nch; ++c) {
-            re += sums[(2 * c) * kMaxProj + 2 * j];
-            im += sums[(2 * c) * kMaxProj + 2 * j + 1];
+        R re = 0, im = 0, e = 0;
+        if (j < np) {
+            for (int c = 0; c < nch; ++c) {
+                re += sums[(2 * c) * kMaxProj + 2 * j];
+                im += sums[(2 * c) * kMaxProj + 2 * j + 1];
+            }
+            e = (R)gp(a.pj.EjN2)[at * kMaxProj + j];
         }
-        const R e = j < np ? (R)gp(a.pj.EjN2)[at * kMaxProj + j] : (R)0;
         gst(reinterpret_cast<V *>(a.D) +
                 ((size_t)sl * a.pj.natoms + at) * kMaxProj + j,
             cmk<V>(e * re, e * im));
@@ -1500,7 +1507,7 @@ __host__ __device__ constexpr int apply_groups(int ns, int spw)
 }
 template <class T> using kptr_t = __attribute__((address_space(4))) const T *;
 
-template <class R, int SPW>
+template <class R, int SPW, int NP>
 __device__ __forceinline__ void kbapply_item(const GArgs &a, const int chunk,
                                              const int grp)
 {
@@ -1528,11 +1535,11 @@ __device__ __forceinline__ void kbapply_item(const GArgs &a, const int chunk,
         if (slot != i)
             continue;
         const int code = gp(a.pj.he_code)[e];
-        R p[kMaxProj];
+        R p[NP];
 #pragma unroll
-        for (int j = 0; j < kMaxProj; ++j)
+        for (int j = 0; j < NP; ++j)
             p[j] = (R)gp(a.pj.he_p)[(size_t)e * kMaxProj + j];
-        // all 9 projectors: past the atom's count both the coefficients
+        // all NP projectors: past the atom's count both the coefficients
         // and the tabulated values are zero
 #pragma unroll
         for (int q = 0; q < SPW; ++q) {
@@ -1540,13 +1547,13 @@ __device__ __forceinline__ void kbapply_item(const GArgs &a, const int chunk,
             if (sl < a.ns) {
                 const kptr_t<R> D =
                     Dall + 2 * ((size_t)sl * a.pj.natoms + at) * kMaxProj;
-                R d[2 * kMaxProj];
+                R d[2 * NP];
 #pragma unroll
-                for (int j = 0; j < 2 * kMaxProj; ++j)
+                for (int j = 0; j < 2 * NP; ++j)
                     d[j] = D[j];
                 V t = czero<V>();
 #pragma unroll
-                for (int j = 0; j < kMaxProj; ++j)
+                for (int j = 0; j < NP; ++j)
                     t = cadd(t, cscale(cmk<V>(d[2 * j], d[2 * j + 1]), p[j]));
                 if (code) {
                     const int kk = (a.sg0 + sl) / a.nstates;

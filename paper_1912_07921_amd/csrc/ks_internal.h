@@ -48,6 +48,7 @@ struct Geo {
 //    hc_atoms[hc_off[c] .. hc_off[c+1]).
 struct ProjDev {
     int natoms = 0;
+    int npmax = kMaxProj;          // most projectors of an atom
     const int *nproj = nullptr;
     const int *npts = nullptr;
     const long *ioff = nullptr;
@@ -286,6 +287,7 @@ struct BArgs {
     const int *off = nullptr;      // [njobs+1] item offsets (device)
     int off_total = 0;             // items over all jobs (host copy)
     int pass = 1;                  // Taylor pass 1..8 of the ETRS step
+    int npmax = kMaxProj;          // most projectors of an atom of any job
 };
 
 int batch_items(int kind, const JobDev &J);

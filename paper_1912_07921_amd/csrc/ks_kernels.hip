@@ -6,24 +6,26 @@
 
 namespace ks {
 
-template <class R, class InT>
+// NP: projectors per atom, 4 where every atom has s and p at most (half the
+// sums, the reduction and the coefficients of the nine) or 9.
+template <class R, class InT, int NP>
 __global__ __launch_bounds__(256) void k_gather(GArgs a)
 {
-    gather_item<R, InT>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+    gather_item<R, InT, NP>(a, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // The same work in the plane order of the work items: workgroup -> (state
 // group, work item), consecutive work items (the chunks of one range of
 // planes) of one state group on one XCD.  Used for launches large enough
 // that the chunks of overlapping spheres would otherwise miss the L2.
-template <class R, class InT>
+template <class R, class InT, int NP>
 __global__ __launch_bounds__(256) void k_gather_planes(GArgs a)
 {
     const int L = xcd_remap(blockIdx.x, gridDim.x);
     const int grp = L / a.pj.ngpairs;
     const int *it = reinterpret_cast<const int *>(a.pj.gpairs) +
                     2 * (L - grp * a.pj.ngpairs);
-    gather_item<R, InT>(a, gp(it)[0], grp, gp(it)[1]);
+    gather_item<R, InT, NP>(a, gp(it)[0], grp, gp(it)[1]);
 }
 
 template <class R>
@@ -37,17 +39,17 @@ extern __shared__ double smem_proj[];
 // (768 threads: three FP64 wavefronts per SIMD without spills)
 constexpr int kSphereWaves = 12;
 
-template <class R, class InT>
+template <class R, class InT, int NP>
 __global__ __launch_bounds__(64 * kSphereWaves) void k_gather_sphere(GArgs a)
 {
-    gather_sphere_item<R, InT>(a, blockIdx.x, blockIdx.y,
+    gather_sphere_item<R, InT, NP>(a, blockIdx.x, blockIdx.y,
                                reinterpret_cast<R *>(smem_proj));
 }
 
-template <class R, int SPW>
+template <class R, int SPW, int NP>
 __global__ __launch_bounds__(kApplyThreads) void k_kbapply(GArgs a)
 {
-    kbapply_item<R, SPW>(a, blockIdx.x, blockIdx.y);
+    kbapply_item<R, SPW, NP>(a, blockIdx.x, blockIdx.y);
 }
 
 // ---------------------------------------------------------------------------
@@ -435,13 +437,15 @@ int gather_chunk_points() { return kGatherChunk; }
 // and 96 workgroups the plain order is 2-10 % faster).
 constexpr long kGatherPlaneOrderMin = 8192;
 // Launches of at most this many (atom, state, chunk) wavefronts give each atom
-// and state one workgroup (k_gather_sphere): 24^3 x 4 states, 72 wavefronts,
-// 8.7 + 4.4 us in two launches -> 8.6; 64^3 x 32, 2304, 13.1 + 5.3 -> 13.6
-// (FP32 13.3 + 5.1 -> 11.5); 48^3 x 64, 3072, 15.6 + 4.6 -> 18.6; 72x60x66 x
-// 40, 3600, 16.1 + 5.3 -> 22.0.
-constexpr long kGatherSphereMax = 3072;
+// and state one workgroup (k_gather_sphere).  Nine projectors: 24^3 x 4 states,
+// 72 wavefronts, 8.7 + 4.4 us in two launches -> 8.6; 64^3 x 32, 2304, 13.1 +
+// 5.3 -> 13.6 (FP32 13.3 + 5.1 -> 11.5); 48^3 x 64, 3072, 15.6 + 4.6 -> 18.6;
+// 72x60x66 x 40, 3600, 16.1 + 5.3 -> 22.0.  Four projectors: 7.5, 11.5 (FP32
+// 10.1), 13.7 us, and 13.8 + 5.7 us in two launches at 3600.
+constexpr long kGatherSphereMax = 3072, kGatherSphereMax4 = 4096;
 
-hipError_t launch_gather(bool mixed, bool in_is_f64, const GArgs &a, int ns,
+template <int NP>
+static hipError_t go_gather(bool mixed, bool in_is_f64, const GArgs &a, int ns,
                          hipStream_t st)
 {
     if (ns <= 0 || a.pj.natoms <= 0)
@@ -452,19 +456,20 @@ hipError_t launch_gather(bool mixed, bool in_is_f64, const GArgs &a, int ns,
     // sums the whole sphere and needs no second launch
     const int W = std::min(a.nchunk, kSphereWaves);
     const size_t rs = mixed ? 4 : 8;
-    const size_t lds = rs * ((size_t)W * kSphereRow +
+    const size_t lds = rs * ((size_t)W * sphere_row(NP) +
                              (size_t)a.nchunk * 2 * kMaxProj);
-    if ((long)a.pj.natoms * ns * a.nchunk <= kGatherSphereMax &&
+    if ((long)a.pj.natoms * ns * a.nchunk <=
+            (NP <= 4 ? kGatherSphereMax4 : kGatherSphereMax) &&
         lds <= kLdsBudget && ns <= 65535) {
         dim3 grid(a.pj.natoms, ns), blk(64 * W);
         if (!mixed)
-            hipLaunchKernelGGL((k_gather_sphere<double, double2>), grid, blk,
+            hipLaunchKernelGGL((k_gather_sphere<double, double2, NP>), grid, blk,
                                lds, st, b);
         else if (in_is_f64)
-            hipLaunchKernelGGL((k_gather_sphere<float, double2>), grid, blk,
+            hipLaunchKernelGGL((k_gather_sphere<float, double2, NP>), grid, blk,
                                lds, st, b);
         else
-            hipLaunchKernelGGL((k_gather_sphere<float, float2>), grid, blk,
+            hipLaunchKernelGGL((k_gather_sphere<float, float2, NP>), grid, blk,
                                lds, st, b);
         return hipGetLastError();
     }
@@ -474,24 +479,24 @@ hipError_t launch_gather(bool mixed, bool in_is_f64, const GArgs &a, int ns,
     if (nblk >= kGatherPlaneOrderMin && nblk <= 0x7fffffffL) {
         dim3 grid((unsigned)nblk);
         if (!mixed)
-            hipLaunchKernelGGL((k_gather_planes<double, double2>), grid, blk,
+            hipLaunchKernelGGL((k_gather_planes<double, double2, NP>), grid, blk,
                                0, st, b);
         else if (in_is_f64)
-            hipLaunchKernelGGL((k_gather_planes<float, double2>), grid, blk,
+            hipLaunchKernelGGL((k_gather_planes<float, double2, NP>), grid, blk,
                                0, st, b);
         else
-            hipLaunchKernelGGL((k_gather_planes<float, float2>), grid, blk,
+            hipLaunchKernelGGL((k_gather_planes<float, float2, NP>), grid, blk,
                                0, st, b);
     } else {
         dim3 grid(a.pj.natoms, ngrp, a.nchunk);
         if (!mixed)
-            hipLaunchKernelGGL((k_gather<double, double2>), grid, blk, 0, st,
+            hipLaunchKernelGGL((k_gather<double, double2, NP>), grid, blk, 0, st,
                                b);
         else if (in_is_f64)
-            hipLaunchKernelGGL((k_gather<float, double2>), grid, blk, 0, st,
+            hipLaunchKernelGGL((k_gather<float, double2, NP>), grid, blk, 0, st,
                                b);
         else
-            hipLaunchKernelGGL((k_gather<float, float2>), grid, blk, 0, st,
+            hipLaunchKernelGGL((k_gather<float, float2, NP>), grid, blk, 0, st,
                                b);
     }
     hipError_t e = hipGetLastError();
@@ -508,7 +513,9 @@ hipError_t launch_gather(bool mixed, bool in_is_f64, const GArgs &a, int ns,
     return hipGetLastError();
 }
 
-hipError_t launch_kbapply(bool mixed, const GArgs &a, int ns, hipStream_t st)
+template <int NP>
+static hipError_t go_kbapply(bool mixed, const GArgs &a, int ns,
+                             hipStream_t st)
 {
     if (ns <= 0 || a.pj.natoms <= 0 || a.pj.nhull <= 0)
         return hipSuccess;
@@ -519,18 +526,31 @@ hipError_t launch_kbapply(bool mixed, const GArgs &a, int ns, hipStream_t st)
     constexpr int SL = KS_APPLY_SPW_LARGE, SS = KS_APPLY_SPW_SMALL,
                   SL32 = KS_APPLY_SPW_LARGE32;
     if (!mixed && spw == SL)
-        hipLaunchKernelGGL((k_kbapply<double, SL>), grid,
+        hipLaunchKernelGGL((k_kbapply<double, SL, NP>), grid,
                            dim3(kApplyThreads), 0, st, b);
     else if (!mixed)
-        hipLaunchKernelGGL((k_kbapply<double, SS>), grid,
+        hipLaunchKernelGGL((k_kbapply<double, SS, NP>), grid,
                            dim3(kApplyThreads), 0, st, b);
     else if (spw == SL32)
-        hipLaunchKernelGGL((k_kbapply<float, SL32>), grid,
+        hipLaunchKernelGGL((k_kbapply<float, SL32, NP>), grid,
                            dim3(kApplyThreads), 0, st, b);
     else
-        hipLaunchKernelGGL((k_kbapply<float, SS>), grid, dim3(kApplyThreads),
+        hipLaunchKernelGGL((k_kbapply<float, SS, NP>), grid, dim3(kApplyThreads),
                            0, st, b);
     return hipGetLastError();
+}
+
+hipError_t launch_gather(bool mixed, bool in_is_f64, const GArgs &a, int ns,
+                         hipStream_t st)
+{
+    return a.pj.npmax <= 4 ? go_gather<4>(mixed, in_is_f64, a, ns, st)
+                           : go_gather<kMaxProj>(mixed, in_is_f64, a, ns, st);
+}
+
+hipError_t launch_kbapply(bool mixed, const GArgs &a, int ns, hipStream_t st)
+{
+    return a.pj.npmax <= 4 ? go_kbapply<4>(mixed, a, ns, st)
+                           : go_kbapply<kMaxProj>(mixed, a, ns, st);
 }
 
 // he_p[e][j] = p_j (without N_j) of entry e's atom at its sphere point, by

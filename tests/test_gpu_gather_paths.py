@@ -1,8 +1,9 @@
 """The projector coefficients from one workgroup per atom and state (few
 states) and from chunk partials in two launches (many) sum the sphere in the
 same order: H.psi of 110 states at once is bitwise that of the states one by
-one, in both precisions, with Bloch phases and with spheres of one chunk and
-of more chunks than the workgroup has wavefronts.  Against the oracle 1e-12
+one, in both precisions, with Bloch phases, with spheres of one chunk and of more
+chunks than the workgroup has wavefronts, with up to one, four and nine
+projectors per atom.  Against the oracle 1e-12
 (FP64) and 1e-5 (mixed), as H.psi elsewhere."""
 import numpy as np
 import pytest
@@ -13,16 +14,19 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("prec,tol", [(0, 1e-12), (1, 1e-5)])
-@pytest.mark.parametrize("rc,natoms,ns,periodic", [
-    (2.4, 2, 110, (0, 0, 0)),      # 15 chunks
-    (2.4, 2, 110, (1, 1, 1)),
-    (0.9, 31, 101, (0, 1, 0))])    # one chunk
-def test_gather_paths_agree(oracle_mod, rc, natoms, ns, periodic, prec, tol):
+@pytest.mark.parametrize("lmax,rc,natoms,ns,periodic", [
+    (2, 2.4, 2, 110, (0, 0, 0)),      # 15 chunks
+    (2, 2.4, 2, 110, (1, 1, 1)),
+    (2, 0.9, 31, 101, (0, 1, 0)),     # one chunk
+    (1, 2.4, 2, 140, (1, 1, 1)),      # four projectors
+    (0, 0.9, 31, 135, (0, 0, 0))])
+def test_gather_paths_agree(oracle_mod, lmax, rc, natoms, ns, periodic, prec,
+                            tol):
     import torch
     from paper_1912_07921_amd import ks
     spec, v, psi = W.tiny(n=(26, 27, 25), h=(0.2, 0.2, 0.2),
                           periodic=periodic, nk=1, nstates=ns, natoms=natoms,
-                          lmax=2, rc=rc, sigma=rc / 4, seed=7)
+                          lmax=lmax, rc=rc, sigma=rc / 4, seed=7)
     o = oracle_mod.Oracle(spec)
     g = ks.Grid(spec, precision=prec)
     g.update_vlocal(torch.from_numpy(v).cuda())
