@@ -90,7 +90,7 @@ struct ks_grid {
     size_t ws_bytes = 0;
     struct {
         size_t t1, t2, t3, half, npart, normpart, D, W, Dpart, rho, vpred,
-            dpart, gpart, dotpart, xpart, step, vhist, veff, pwork, vh, cpart,
+            dpart, gpart, xpart, step, vhist, veff, pwork, vh, cpart,
             cnl, normchk, v32, total;
     } lay{};
     int ntiles_max = 64;
@@ -507,8 +507,9 @@ Shape pick_shape(const ks_grid *g, int ns, int rpt_only = 0)
                 // (and the current's)
                 const int room =
                     rpt == 2 || rpt_only > 0 ? 8 : (mx ? 16 : 12);
+                // (a workgroup takes ceil(w / 4) of every SIMD's)
                 const int fit = std::max(
-                    1, std::min(room / std::max(1, w),
+                    1, std::min(room / 4 / ((w + 3) / 4),
                                 (int)(kLdsBudget / lds)));
                 const long per_cu = std::min<long>(
                     fit, (nwg + kCUs - 1) / kCUs);
@@ -633,18 +634,18 @@ void layout(ks_grid *g)
     g->lay.rho = take(N * 8);
     g->lay.vpred = take(N * 8);
     g->lay.dpart = take(ndb * 3 * 8);
-    // Gram: split the grid so that about 2048 workgroups share the work
-    // (gram_tile x gram_tile state tiles per k-point), each slice at least
-    // 512 points
+    // Gram: split the grid so that about 1024 workgroups share the work
+    // (gram_tile x gram_tile state tiles on and above the diagonal, per
+    // k-point; each slice leaves a partial matrix), each slice at least 512
+    // points
     {
         const long nt = (g->ns + gram_tile(g->ns) - 1) / gram_tile(g->ns);
-        const long tiles = nt * nt * g->nk;
-        const long want = std::max<long>(1, (2048 + tiles - 1) / tiles);
+        const long tiles = nt * (nt + 1) / 2 * g->nk;
+        const long want = std::max<long>(1, (1024 + tiles - 1) / tiles);
         const long most = std::max<long>(1, (long)N / 512);
         g->gram_ksplit = (int)std::max<long>(1, std::min(want, most));
     }
     g->lay.gpart = take((size_t)g->gram_ksplit * g->nk * g->ns * g->ns * 16);
-    g->lay.dotpart = take(S * g->norm_chunks * 16);
     g->lay.xpart = take(ndb * 8);
     g->lay.step = take(sizeof(int));
     g->lay.vhist = take(4 * N * 8);
@@ -1542,38 +1543,32 @@ int ks_energy(ks_grid *g, const void *d_psi, const double *d_vion, double t,
         return rc;
     if (g->mixed)
         return fail(KS_E_UNSUPPORTED, "ks_energy runs on an FP64 grid");
-    // H[v_ion] psi for every k into the half-step buffer
+    // <psi|H[v_ion]|psi> of every state: the H.psi pass keeps the sums of
+    // its tiles and stores nothing (48^3, 4 k x 64 states: passes of 4 x 73
+    // us and a product of 148 us over both arrays -> one pass of 275 us)
     double A[3];
     laser_A(g, t, A);
-    double2 *hp = wsp<double2>(g, g->lay.half);
     const double2 *psi = static_cast<const double2 *>(d_psi);
-    void *D = g->ws + g->lay.D;
     const long N = g->geo.N;
-    for (int k = 0; k < g->nk; ++k) {
-        GArgs ga = base_gargs(g);
-        ga.in = psi + (size_t)k * g->ns * N;
-        ga.D = D;
-        ga.sg0 = k * g->ns;
-        KS_HIP(launch_gather(false, true, ga, g->ns, g->stream));
-        KS_HIP(launch_kbapply(false, ga, g->ns, g->stream));
-        HArgs a = base_hargs(g);
-        call_shape(g, g->ns, &a);
-        a.in = ga.in;
-        a.out = hp + (size_t)k * g->ns * N;
-        a.v = d_vion;
-        a.A[0] = A[0];
-        a.A[1] = A[1];
-        a.A[2] = A[2];
-        a.a2half = 0.5 * (A[0] * A[0] + A[1] * A[1] + A[2] * A[2]);
-
-        a.sg0 = k * g->ns;
-        KS_HIP(launch_hpsi(kApply, false, true, a, g->ns, g->stream));
-    }
-    double2 *dp = wsp<double2>(g, g->lay.dotpart);
-    KS_HIP(launch_dot_partial(g->geo, psi, hp, g->stot, g->norm_chunks, dp,
-                              g->stream));
-    std::vector<double2> hdp((size_t)g->stot * g->norm_chunks);
-    KS_HIP(hipMemcpyAsync(hdp.data(), dp, hdp.size() * sizeof(double2),
+    const int S = g->stot;
+    GArgs ga = base_gargs(g);
+    ga.in = psi;
+    ga.D = g->ws + g->lay.D;
+    KS_HIP(launch_gather(false, true, ga, S, g->stream));
+    KS_HIP(launch_kbapply(false, ga, S, g->stream));
+    HArgs ha = base_hargs(g);
+    ha.in = psi;
+    ha.v = d_vion;
+    for (int d = 0; d < 3; ++d)
+        ha.A[d] = A[d];
+    ha.a2half = half_a2(A);
+    ha.normpart = wsp<double>(g, g->lay.normpart);
+    KS_HIP(launch_hpsi(kEnergy, false, true, ha, S, g->stream));
+    double *de = wsp<double>(g, g->lay.normchk);
+    KS_HIP(launch_norm_finalize(ha.normpart, S, ha.ntile_y * ha.nzc, 1.0, de,
+                                g->stream));
+    std::vector<double> he(S);
+    KS_HIP(hipMemcpyAsync(he.data(), de, S * sizeof(double),
                           hipMemcpyDeviceToHost, g->stream));
     double ex = 0.0, eh = 0.0;
     const int nb = density_blocks(N);
@@ -1608,12 +1603,8 @@ int ks_energy(ks_grid *g, const void *d_psi, const double *d_vion, double t,
     KS_HIP(hipStreamSynchronize(g->stream));
     const double h3 = g->geo.h[0] * g->geo.h[1] * g->geo.h[2];
     double e = 0.0;
-    for (int s = 0; s < g->stot; ++s) {
-        double acc = 0.0;
-        for (int c = 0; c < g->norm_chunks; ++c)
-            acc += hdp[(size_t)s * g->norm_chunks + c].x;
-        e += g->wocc[s] * acc * h3;
-    }
+    for (int s = 0; s < S; ++s)
+        e += g->wocc[s] * he[s] * h3;
     if (g->xc) {
         double sx = 0.0;
         for (int b = 0; b < nb; ++b)

@@ -531,6 +531,7 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
     unsigned char *smem_raw = reinterpret_cast<unsigned char *>(smem_d2);
     constexpr bool FIN = MODE == kFinal || MODE == kFinalPred;
     constexpr bool CUR = MODE == kCurrent;
+    constexpr bool ENE = MODE == kEnergy;
 
     const int nx = a.geo.nx, ny = a.geo.ny, nz = a.geo.nz;
     const int P = nx * ny;
@@ -605,7 +606,7 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
     const void *vptr = CUR ? nullptr
                            : (V32 ? (const void *)a.v32 : (const void *)a.v);
     using OutT = typename std::conditional<MODE == kTerm, TT, double2>::type;
-    OutT *out = CUR ? nullptr : reinterpret_cast<OutT *>(a.out) + sN;
+    OutT *out = CUR || ENE ? nullptr : reinterpret_cast<OutT *>(a.out) + sN;
     const BufRes rw = buf_any(Wst, proj);
     auto off_of = [&](int r, size_t elem) -> unsigned {
         return elem == 16 ? p16[r] : (elem == 8 ? p8[r] : p4[r]);
@@ -1069,14 +1070,17 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
         if constexpr (!CUR) {
 #pragma unroll
             for (int r = 0; r < RPT; ++r) {
-                const BufRes rout = buf_any(out + so, emit);
+                const BufRes rout = buf_any(out + so, emit && !ENE);
                 const unsigned off = off_of(r, sizeof(OutT));
                 // FP64: potential and KB term of the finished point
                 V hp = done[r];
                 if constexpr (SC)
                     hp = cadd(cfma((R)(sv[UV][r] + Avec.w), cdone[r], hp),
                               skb[UV][r]);
-                if constexpr (MODE == kApply) {
+                if constexpr (ENE) {
+                    if (act[r] && emit)
+                        nrm += cdone[r].x * hp.x + cdone[r].y * hp.y;
+                } else if constexpr (MODE == kApply) {
                     bst<double2>(rout, off, (double)hp.x, (double)hp.y);
                 } else if constexpr (MODE == kTerm) {
                     bst<TT>(rout, off, -sc * hp.y, sc * hp.x);
@@ -1141,7 +1145,7 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
         if (z + 3 < zend)
             plane_step(std::integral_constant<int, 3>{}, z + 3);
     }
-    if constexpr (MODE == kFinal) {
+    if constexpr (MODE == kFinal || ENE) {
         if (!a.normpart)
             return;
         __syncthreads();

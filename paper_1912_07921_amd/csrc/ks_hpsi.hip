@@ -109,6 +109,7 @@ hipError_t launch_hpsi(int mode, bool mixed, bool in_is_f64, const HArgs &a,
     switch (mode) {
     case kApply: return go_hpsi<double, double2, double2, kApply>(a, ns, st);
     case kTerm: return go_hpsi<double, double2, double2, kTerm>(a, ns, st);
+    case kEnergy: return go_hpsi<double, double2, double2, kEnergy>(a, ns, st);
     case kFinal: return go_hpsi<double, double2, double2, kFinal>(a, ns, st);
     case kFinalPred:
         return go_hpsi<double, double2, double2, kFinalPred>(a, ns, st);

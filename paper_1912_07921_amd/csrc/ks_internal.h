@@ -22,9 +22,11 @@ enum Mode : int {
                      // density partials and norms of out        (complex128)
     kFinalPred = 3,  // as kFinal, plus the predictor
                      // base + 2 t1 + 4 t2 + 8 t3 + 16 t4 feeds the density
-    kCurrent = 4     // no output: per tile, sum over its points of
+    kCurrent = 4,    // no output: per tile, sum over its points of
                      // Im(conj(psi) [H_stencil, r_a] psi), a = x, y, z,
                      // into normpart[tile][3] (FP64 only)
+    kEnergy = 5      // no output: per tile, sum over its points of
+                     // Re(conj(in) H in), into normpart[tile] (FP64 only)
 };
 
 struct Geo {
@@ -243,9 +245,6 @@ hipError_t launch_norm_finalize_batch(const NormJob *jobs, int njobs,
 hipError_t launch_gram(const Geo &g, const double2 *psi, int nk, int ns,
                        double2 *part, int ksplit, double2 *out,
                        hipStream_t st);
-hipError_t launch_dot_partial(const Geo &g, const double2 *a,
-                              const double2 *b, int ns, int nchunks,
-                              double2 *part, hipStream_t st);
 hipError_t launch_vcombine(long N, int h, const double *const src[4],
                            const double w[4], double *out, hipStream_t st);
 hipError_t launch_exchange_partial(const Geo &g, const double *rho,

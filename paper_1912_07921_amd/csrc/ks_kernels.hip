@@ -278,19 +278,50 @@ __global__ __launch_bounds__(256) void k_kick(Geo G, double2 *psi,
 
 // ---------------------------------------------------------------------------
 // Gram matrix partials on the FP64 matrix cores: part[ks][k][i][j] = sum
-// over the ks-th slice of the grid of conj(psi_ki) psi_kj.  A workgroup
-// (four wavefronts) owns a T x T tile of (i, j) (T = 64, or 32 for few
-// states), each wavefront a T/2 x T/2 quarter as blocks of 16 x 16
-// accumulated by
-// v_mfma_f64_16x16x4f64 (D[16][16] += A[16][4] B[4][16], four grid points
-// per instruction): Re G = Ar^T Ar + Ai^T Ai and Im G = Ar^T Ai - Ai^T Ar,
-// with A the states' values at the points.  32 points of the tile's T + T
+// over the ks-th slice of the grid of conj(psi_ki) psi_kj for j >= i (the
+// rest is its conjugate).  A workgroup (four wavefronts) owns a T x T tile of
+// (i, j), ti <= tj (T = 64, or 32 for few states), as blocks of 16 x 16
+// accumulated by v_mfma_f64_16x16x4f64 (D[16][16] += A[16][4] B[4][16], four
+// grid points per instruction): Re G = Ar^T Ar + Ai^T Ai and Im G = Ar^T Ai -
+// Ai^T Ar, with A the states' values at the points.  32 points of the tile's
 // states are staged through LDS per round (coalesced rows of 512 bytes).
+// A tile off the diagonal gives each wavefront a quarter; a tile on it has
+// one set of states (half the loads and the LDS) and only the blocks on and
+// above the diagonal, which every wavefront accumulates over its quarter of
+// the points (10 of 16 blocks at T = 64); the four sums meet in LDS.
+// The matrix pipe and the stage loads (one round in flight) bound it: 48^3, 4
+// k x 64 states 408 + 71 us with every block computed, both copies of a
+// diagonal tile staged and one thread per element of the 512 slices' sum, 281
+// + 11 us so.
 // Operand layout on gfx950: lane l holds A[l % 16][l / 16] and
 // B[l / 16][l % 16]; D[4 r + l / 16][l % 16] is element r of lane l's
 // accumulator.
 // ---------------------------------------------------------------------------
 constexpr int kGK = 32;          // points per LDS stage
+
+__device__ __forceinline__ void gram_block(double2 a, double2 b, gd4_t &re,
+                                           gd4_t &im)
+{
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, re, 0, 0, 0);
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.y, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, im, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.x, im, 0, 0, 0);
+}
+
+// the states st .. st + kGT - 1 at kGK points from g0 (zero past the ends)
+template <int kGT>
+__device__ __forceinline__ void gram_stage(double2 (&s)[kGT][kGK + 1],
+                                           const double2 *pk, long N, int st,
+                                           int ns, long g0, long ge)
+{
+#pragma unroll
+    for (int u = 0; u < kGT / 8; ++u) {
+        const int r = (threadIdx.x >> 5) + 8 * u, c = threadIdx.x & 31;
+        const long g = g0 + c;
+        s[r][c] = (st + r < ns && g < ge) ? pk[(size_t)(st + r) * N + g]
+                                          : make_double2(0.0, 0.0);
+    }
+}
 
 template <int kGT>
 __global__ __launch_bounds__(256) void k_gram_partial(Geo G,
@@ -299,38 +330,88 @@ __global__ __launch_bounds__(256) void k_gram_partial(Geo G,
                                                       double2 *part)
 {
     constexpr int B = kGT / 32;      // 16 x 16 blocks per wavefront side
+    constexpr int D = kGT / 16;      // and per tile side
+    constexpr int ND = D * (D + 1) / 2;
     __shared__ double2 sa[kGT][kGK + 1];
     __shared__ double2 sb[kGT][kGK + 1];
     const int ntile = (ns + kGT - 1) / kGT;
-    const int ti = blockIdx.x % ntile, tj = blockIdx.x / ntile;
+    // tile pair blockIdx.x of the upper triangle, row by row
+    int ti = 0, rest = blockIdx.x;
+    while (rest >= ntile - ti) {
+        rest -= ntile - ti;
+        ++ti;
+    }
+    const int tj = ti + rest;
     const int kk = blockIdx.y;
     const int ks = blockIdx.z;
     const long slice = (G.N + ksplit - 1) / ksplit;
     const long gb = ks * slice, ge = min(G.N, gb + slice);
     const double2 *pk = psi + (size_t)kk * ns * G.N;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int r0 = (wave >> 1) * (kGT / 2), c0 = (wave & 1) * (kGT / 2);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int li = lane & 15, lk = lane >> 4;
+    double2 *out = part + ((size_t)ks * gridDim.y + kk) * ns * ns;
+    if (ti == tj) {
+        gd4_t re[ND], im[ND];
+#pragma unroll
+        for (int b = 0; b < ND; ++b)
+            re[b] = im[b] = gd4_t{0.0, 0.0, 0.0, 0.0};
+        for (long g0 = gb; g0 < ge; g0 += kGK) {
+            gram_stage<kGT>(sa, pk, G.N, ti * kGT, ns, g0, ge);
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < kGK / 16; ++q) {
+                const int k4 = 8 * wave + 4 * q;
+                double2 v[D];
+#pragma unroll
+                for (int u = 0; u < D; ++u)
+                    v[u] = sa[16 * u + li][k4 + lk];
+                int b = 0;
+#pragma unroll
+                for (int u = 0; u < D; ++u)
+#pragma unroll
+                    for (int w = u; w < D; ++w, ++b)
+                        gram_block(v[u], v[w], re[b], im[b]);
+            }
+            __syncthreads();
+        }
+        // the wavefronts' sums in order; sb holds one block of each
+        double2 *sum = &sb[0][0];
+        int b = 0;
+#pragma unroll
+        for (int u = 0; u < D; ++u)
+#pragma unroll
+            for (int w = u; w < D; ++w, ++b) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    sum[wave * 256 + r * 64 + lane] =
+                        make_double2(re[b][r], im[b][r]);
+                __syncthreads();
+                const int t = threadIdx.x;         // element r * 64 + lane
+                double2 s = sum[t];
+                for (int q = 1; q < 4; ++q) {
+                    const double2 v = sum[q * 256 + t];
+                    s.x += v.x;
+                    s.y += v.y;
+                }
+                const int i = ti * kGT + 16 * u + 4 * (t >> 6) +
+                              ((t & 63) >> 4);
+                const int j = ti * kGT + 16 * w + (t & 15);
+                if (i < ns && j < ns && i <= j)
+                    out[(size_t)i * ns + j] = s;
+                __syncthreads();
+            }
+        return;
+    }
+    const int r0 = (wave >> 1) * (kGT / 2), c0 = (wave & 1) * (kGT / 2);
     gd4_t re[B][B], im[B][B];
 #pragma unroll
     for (int u = 0; u < B; ++u)
 #pragma unroll
-        for (int w = 0; w < B; ++w) {
-            re[u][w] = gd4_t{0.0, 0.0, 0.0, 0.0};
-            im[u][w] = gd4_t{0.0, 0.0, 0.0, 0.0};
-        }
+        for (int w = 0; w < B; ++w)
+            re[u][w] = im[u][w] = gd4_t{0.0, 0.0, 0.0, 0.0};
     for (long g0 = gb; g0 < ge; g0 += kGK) {
-#pragma unroll
-        for (int u = 0; u < kGT / 8; ++u) {
-            const int r = (tid >> 5) + 8 * u, c = tid & 31;   // kGK = 32
-            const long g = g0 + c;
-            const int si = ti * kGT + r, sj = tj * kGT + r;
-            sa[r][c] = (si < ns && g < ge) ? pk[(size_t)si * G.N + g]
-                                           : make_double2(0.0, 0.0);
-            sb[r][c] = (sj < ns && g < ge) ? pk[(size_t)sj * G.N + g]
-                                           : make_double2(0.0, 0.0);
-        }
+        gram_stage<kGT>(sa, pk, G.N, ti * kGT, ns, g0, ge);
+        gram_stage<kGT>(sb, pk, G.N, tj * kGT, ns, g0, ge);
         __syncthreads();
 #pragma unroll
         for (int k4 = 0; k4 < kGK; k4 += 4) {
@@ -343,16 +424,8 @@ __global__ __launch_bounds__(256) void k_gram_partial(Geo G,
 #pragma unroll
             for (int u = 0; u < B; ++u)
 #pragma unroll
-                for (int w = 0; w < B; ++w) {
-                    re[u][w] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                        a[u].x, b[w].x, re[u][w], 0, 0, 0);
-                    re[u][w] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                        a[u].y, b[w].y, re[u][w], 0, 0, 0);
-                    im[u][w] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                        a[u].x, b[w].y, im[u][w], 0, 0, 0);
-                    im[u][w] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                        -a[u].y, b[w].x, im[u][w], 0, 0, 0);
-                }
+                for (int w = 0; w < B; ++w)
+                    gram_block(a[u], b[w], re[u][w], im[u][w]);
         }
         __syncthreads();
     }
@@ -365,49 +438,46 @@ __global__ __launch_bounds__(256) void k_gram_partial(Geo G,
                 const int i = ti * kGT + r0 + 16 * u + 4 * r + lk;
                 const int j = tj * kGT + c0 + 16 * w + li;
                 if (i < ns && j < ns)
-                    part[(((size_t)ks * gridDim.y + kk) * ns + i) * ns + j] =
+                    out[(size_t)i * ns + j] =
                         make_double2(re[u][w][r], im[u][w][r]);
             }
 }
 
-__global__ __launch_bounds__(256) void k_gram_finalize(const double2 *part,
-                                                       long count, int ksplit,
-                                                       double h3,
-                                                       double2 *out)
-{
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= count)
-        return;
-    double2 s = make_double2(0.0, 0.0);
-    for (int k = 0; k < ksplit; ++k) {
-        double2 v = part[(size_t)k * count + i];
-        s.x += v.x;
-        s.y += v.y;
-    }
-    out[i] = make_double2(h3 * s.x, h3 * s.y);
-}
+// G[k][i][j], j >= i, and its mirror: 16 threads share the slices of an
+// element (in order, then in order over the threads).
+constexpr int kGfElems = 16, kGfParts = 16;
 
-// per-state partial sums of conj(a) b over chunks of the grid
-__global__ __launch_bounds__(256) void k_dot_partial(Geo G, const double2 *a,
-                                                     const double2 *b,
-                                                     int nchunks,
-                                                     double2 *part)
+__global__ __launch_bounds__(kGfElems *kGfParts) void k_gram_finalize(
+    const double2 *part, int ns, long count, int ksplit, double h3,
+    double2 *out)
 {
-    __shared__ double sbuf[4 * 2];
-    const int s = blockIdx.y;
-    const long chunk = (G.N + nchunks - 1) / nchunks;
-    const long gb = (long)blockIdx.x * chunk;
-    const long ge = min(G.N, gb + chunk);
-    const double2 *pa = a + (size_t)s * G.N, *pb = b + (size_t)s * G.N;
-    double acc[2] = {0.0, 0.0};
-    for (long g = gb + threadIdx.x; g < ge; g += blockDim.x) {
-        double2 u = pa[g], v = pb[g];
-        acc[0] += u.x * v.x + u.y * v.y;
-        acc[1] += u.x * v.y - u.y * v.x;
+    __shared__ double2 s[kGfParts][kGfElems];
+    const int e = threadIdx.x % kGfElems, q = threadIdx.x / kGfElems;
+    const long i = (long)blockIdx.x * kGfElems + e;
+    const int row = (int)(i / ns % ns), col = (int)(i % ns);
+    const bool on = i < count && row <= col;
+    double2 a = make_double2(0.0, 0.0);
+    const int per = (ksplit + kGfParts - 1) / kGfParts;
+    if (on)
+        for (int k = q * per; k < min(ksplit, (q + 1) * per); ++k) {
+            const double2 v = part[(size_t)k * count + i];
+            a.x += v.x;
+            a.y += v.y;
+        }
+    s[q][e] = a;
+    __syncthreads();
+    if (q != 0 || !on)
+        return;
+    for (int p = 1; p < kGfParts; ++p) {
+        a.x += s[p][e].x;
+        a.y += s[p][e].y;
     }
-    block_sum<double, 2>(acc, sbuf);
-    if (threadIdx.x == 0)
-        part[(size_t)s * nchunks + blockIdx.x] = make_double2(acc[0], acc[1]);
+    a.x *= h3;
+    a.y *= h3;
+    out[i] = a;
+    if (row < col)
+        out[i + (long)(col - row) * ns - (col - row)] =
+            make_double2(a.x, -a.y);
 }
 
 // partial sums of rho^(4/3) (exchange energy)
@@ -762,7 +832,7 @@ hipError_t launch_gram(const Geo &g, const double2 *psi, int nk, int ns,
 {
     const int T = gram_tile(ns);
     const int ntile = (ns + T - 1) / T;
-    dim3 grid(ntile * ntile, nk, ksplit);
+    dim3 grid(ntile * (ntile + 1) / 2, nk, ksplit);
     if (T == 64)
         hipLaunchKernelGGL((k_gram_partial<64>), grid, dim3(256), 0, st, g,
                            psi, ns, ksplit, part);
@@ -774,19 +844,9 @@ hipError_t launch_gram(const Geo &g, const double2 *psi, int nk, int ns,
         return e;
     const long count = (long)nk * ns * ns;
     double h3 = g.h[0] * g.h[1] * g.h[2];
-    hipLaunchKernelGGL(k_gram_finalize, dim3((unsigned)((count + 255) / 256)),
-                       dim3(256), 0, st, part, count, ksplit, h3, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_dot_partial(const Geo &g, const double2 *a,
-                              const double2 *b, int ns, int nchunks,
-                              double2 *part, hipStream_t st)
-{
-    if (ns <= 0)
-        return hipSuccess;
-    hipLaunchKernelGGL(k_dot_partial, dim3(nchunks, ns), dim3(256), 0, st, g,
-                       a, b, nchunks, part);
+    hipLaunchKernelGGL(
+        k_gram_finalize, dim3((unsigned)((count + kGfElems - 1) / kGfElems)),
+        dim3(kGfElems * kGfParts), 0, st, part, ns, count, ksplit, h3, out);
     return hipGetLastError();
 }
 

@@ -32,10 +32,14 @@ constexpr int kCurThreads = 256;
 // loaded and evaluated once for C_j and the three D_ja):
 // nl[(sl * natoms + at) * 3 + a] = 2 h^3 sum_j N_j^2 h^3 E_j
 // Im(conj(C_j) D_ja).
+// NP: projectors per atom, 4 where none has more (the sums over the workgroup
+// are most of the time: 48^3 x 256 states, 16 atoms, 208 us with nine, 90 with
+// four).
+template <int NP>
 __global__ __launch_bounds__(kCurThreads) void k_current_nl(CurArgs a)
 {
     // per projector: C_j, D_jx, D_jy, D_jz, re and im
-    constexpr int NV = 8 * kMaxProj;
+    constexpr int NV = 8 * NP;
     __shared__ double sbuf[(kCurThreads / 64) * NV];
     const Geo G = a.geo;
     const ProjDev &pj = a.pj;
@@ -65,13 +69,13 @@ __global__ __launch_bounds__(kCurThreads) void k_current_nl(CurArgs a)
             axis_coord(G.ny, G.h[1], G.per[1], iy) + ty * Ly - ap.y,
             axis_coord(G.nz, G.h[2], G.per[2], iz) + tz * Lz - ap.z};
         const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
-        double p[kMaxProj];
-        proj_shape<double>(d[0], d[1], d[2], r2, ar, np, p);
+        double p[NP];
+        proj_shape<double, NP>(d[0], d[1], d[2], r2, ar, np, p);
         double2 v = gld(psi + gi);
         if (code)
             v = cmul(v, shift_phase<double2>(a.kph + 3 * kk, code));
 #pragma unroll
-        for (int j = 0; j < kMaxProj; ++j) {
+        for (int j = 0; j < NP; ++j) {
             const double px = p[j] * v.x, py = p[j] * v.y;
             acc[8 * j] += px;
             acc[8 * j + 1] += py;
@@ -168,8 +172,12 @@ hipError_t launch_current_nl(const CurArgs &a, int ns, hipStream_t st)
 {
     if (ns <= 0 || a.pj.natoms == 0)
         return hipSuccess;
-    hipLaunchKernelGGL(k_current_nl, dim3(a.pj.natoms, ns),
-                       dim3(kCurThreads), 0, st, a);
+    if (a.pj.npmax <= 4)
+        hipLaunchKernelGGL(k_current_nl<4>, dim3(a.pj.natoms, ns),
+                           dim3(kCurThreads), 0, st, a);
+    else
+        hipLaunchKernelGGL(k_current_nl<kMaxProj>, dim3(a.pj.natoms, ns),
+                           dim3(kCurThreads), 0, st, a);
     return hipGetLastError();
 }
 
