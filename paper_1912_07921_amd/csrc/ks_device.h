@@ -1445,6 +1445,8 @@ __device__ __forceinline__ void gather_sphere_item(const GArgs &a,
                 sum += red[lane * 65 + r];
             sums[ch * 2 * kMaxProj + lane] = sum;
         }
+        // the rows are read before the next chunk's values go there
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
