@@ -22,6 +22,8 @@
 
 #include "ks_device.h"
 
+#include <climits>
+
 namespace ks {
 namespace {
 
@@ -120,33 +122,37 @@ __global__ __launch_bounds__(kCurThreads) void k_current_nl(CurArgs a)
 // f(0) when subtract is set (else 0).  Mode 0 (strength function):
 // out[i] = (2 w / (pi kappa)) Im F with s = +1; mode 1 (conductivity):
 // out[2i], out[2i+1] = F / E0 with s = -1.
-// A wavefront per frequency, a lane per sample: the sines and cosines of FP64
-// arguments are what it computes, and one thread per frequency left all but
-// eight workgroups' worth of the chip idle (501 samples, 2000 frequencies: 135
-// -> 7 us).  The workgroup's damped samples are formed once, in LDS.
-constexpr int kFtThreads = 256, kFtWaves = kFtThreads / 64;
+// Its sines and cosines of FP64 arguments are what it computes.  LANES lanes
+// of a wavefront share the samples of a frequency: one thread per frequency
+// left all but eight workgroups' worth of the chip idle (501 samples, 2000
+// frequencies: 135 -> 7 us with 64).  The workgroup's damped samples are
+// formed once, in LDS.
+constexpr int kFtThreads = 256;
 
+// (Int: long where an int would pass its range in the last block)
+template <int LANES, class Int>
 __global__ __launch_bounds__(kFtThreads) void k_damped_ft(
-    const double *f, int nt, int stride, double dt, double scale,
+    const double *f, Int nt, int stride, double dt, double scale,
     double gamma, const double *w, int nw, int mode, double *out)
 {
     __shared__ double amp[kFtThreads];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int i = blockIdx.x * kFtWaves + wave;
-    const double om = i < nw ? w[i] : 0.0;
+    constexpr int kFreqs = kFtThreads / LANES;
+    const int lane = threadIdx.x % LANES;
+    const unsigned i = blockIdx.x * kFreqs + threadIdx.x / LANES;
+    const double om = i < (unsigned)nw ? w[i] : 0.0;
     const double f0 = mode == 0 ? f[0] : 0.0;
     const double s = mode == 0 ? 1.0 : -1.0;
     double re = 0.0, im = 0.0;
-    for (int n0 = 0; n0 < nt; n0 += kFtThreads) {
-        const int n = n0 + (int)threadIdx.x;
+    for (Int n0 = 0; n0 < nt; n0 += kFtThreads) {
+        const Int n = n0 + (int)threadIdx.x;
         if (n < nt) {
             const double wt = (n == 0 || n == nt - 1) ? 0.5 : 1.0;
             amp[threadIdx.x] = wt * (f[(long)n * stride] - f0) *
                                exp(-gamma * (n * dt));
         }
         __syncthreads();
-        const int m = min(kFtThreads, nt - n0);
-        for (int l = lane; l < m; l += 64) {
+        const int m = (int)min((Int)kFtThreads, nt - n0);
+        for (int l = lane; l < m; l += LANES) {
             double sn, cs;
             sincos(s * om * ((n0 + l) * dt), &sn, &cs);
             re += amp[l] * cs;
@@ -154,15 +160,20 @@ __global__ __launch_bounds__(kFtThreads) void k_damped_ft(
         }
         __syncthreads();
     }
-    re = wave_sum(re) * dt;
-    im = wave_sum(im) * dt;
-    if (lane != 0 || i >= nw)
+#pragma unroll
+    for (int off = LANES / 2; off >= 1; off >>= 1) {
+        re += __shfl_xor(re, off, 64);
+        im += __shfl_xor(im, off, 64);
+    }
+    re *= dt;
+    im *= dt;
+    if (lane != 0 || i >= (unsigned)nw)
         return;
     if (mode == 0) {
         out[i] = 2.0 * om / M_PI * im / scale;
     } else {
-        out[2 * i] = re / scale;
-        out[2 * i + 1] = im / scale;
+        out[2L * i] = re / scale;
+        out[2L * i + 1] = im / scale;
     }
 }
 
@@ -181,15 +192,42 @@ hipError_t launch_current_nl(const CurArgs &a, int ns, hipStream_t st)
     return hipGetLastError();
 }
 
+// Lanes per frequency: no more than samples, and no more than give the chip
+// its 256 x 2048 threads (calls with 64 throughout: 16 samples on 10^6
+// frequencies 381 us, with one 60; 501 samples on 200000 280, with two 258, with
+// one 295; 64 on 10^6 380, with one 160).
+constexpr long kFtChip = 256L * 2048;
+
+template <int LANES, class Int>
+static void go_damped_ft(const double *f, int nt, int stride, double dt,
+                         double scale, double gamma, const double *w, int nw,
+                         int mode, double *out, hipStream_t st)
+{
+    if constexpr (LANES > 1) {
+        if (LANES > nt || (long)nw * LANES > kFtChip) {
+            go_damped_ft<LANES / 2, Int>(f, nt, stride, dt, scale, gamma, w,
+                                         nw, mode, out, st);
+            return;
+        }
+    }
+    const long blocks = ((long)nw * LANES + kFtThreads - 1) / kFtThreads;
+    hipLaunchKernelGGL((k_damped_ft<LANES, Int>), dim3((unsigned)blocks),
+                       dim3(kFtThreads), 0, st, f, nt, stride, dt, scale,
+                       gamma, w, nw, mode, out);
+}
+
 hipError_t launch_damped_ft(const double *f, int nt, int stride, double dt,
                             double scale, double gamma, const double *w,
                             int nw, int mode, double *out, hipStream_t st)
 {
     if (nw <= 0)
         return hipSuccess;
-    hipLaunchKernelGGL(k_damped_ft, dim3((nw + kFtWaves - 1) / kFtWaves),
-                       dim3(kFtThreads), 0, st, f, nt, stride, dt, scale,
-                       gamma, w, nw, mode, out);
+    if (nt > INT_MAX - kFtThreads)
+        go_damped_ft<1, long>(f, nt, stride, dt, scale, gamma, w, nw, mode,
+                              out, st);
+    else
+        go_damped_ft<64, int>(f, nt, stride, dt, scale, gamma, w, nw, mode,
+                              out, st);
     return hipGetLastError();
 }
 
