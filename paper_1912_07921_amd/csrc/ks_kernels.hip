@@ -443,32 +443,36 @@ __global__ __launch_bounds__(256) void k_gram_partial(Geo G,
             }
 }
 
-// G[k][i][j], j >= i, and its mirror: 16 threads share the slices of an
+// G[k][i][j], j >= i, and its mirror: PARTS threads share the slices of an
 // element (in order, then in order over the threads).
-constexpr int kGfElems = 16, kGfParts = 16;
+constexpr int kGfThreads = 256, kGramParts = 16;
 
-__global__ __launch_bounds__(kGfElems *kGfParts) void k_gram_finalize(
+template <int PARTS>
+__global__ __launch_bounds__(kGfThreads) void k_gram_finalize(
     const double2 *part, int ns, long count, int ksplit, double h3,
     double2 *out)
 {
-    __shared__ double2 s[kGfParts][kGfElems];
-    const int e = threadIdx.x % kGfElems, q = threadIdx.x / kGfElems;
-    const long i = (long)blockIdx.x * kGfElems + e;
+    constexpr int kElems = kGfThreads / PARTS;
+    __shared__ double2 s[PARTS][kElems];
+    const int e = threadIdx.x % kElems, q = threadIdx.x / kElems;
+    const long i = (long)blockIdx.x * kElems + e;
     const int row = (int)(i / ns % ns), col = (int)(i % ns);
     const bool on = i < count && row <= col;
     double2 a = make_double2(0.0, 0.0);
-    const int per = (ksplit + kGfParts - 1) / kGfParts;
+    const int per = (ksplit + PARTS - 1) / PARTS;
     if (on)
         for (int k = q * per; k < min(ksplit, (q + 1) * per); ++k) {
             const double2 v = part[(size_t)k * count + i];
             a.x += v.x;
             a.y += v.y;
         }
-    s[q][e] = a;
-    __syncthreads();
+    if constexpr (PARTS > 1) {
+        s[q][e] = a;
+        __syncthreads();
+    }
     if (q != 0 || !on)
         return;
-    for (int p = 1; p < kGfParts; ++p) {
+    for (int p = 1; p < PARTS; ++p) {
         a.x += s[p][e].x;
         a.y += s[p][e].y;
     }
@@ -844,9 +848,19 @@ hipError_t launch_gram(const Geo &g, const double2 *psi, int nk, int ns,
         return e;
     const long count = (long)nk * ns * ns;
     double h3 = g.h[0] * g.h[1] * g.h[2];
-    hipLaunchKernelGGL(
-        k_gram_finalize, dim3((unsigned)((count + kGfElems - 1) / kGfElems)),
-        dim3(kGfElems * kGfParts), 0, st, part, ns, count, ksplit, h3, out);
+    // one thread per element where the slices are few, as they are for many
+    // states: sixteen would idle there, and from 2^14 states on pass the 2^32
+    // threads of a launch
+    const int parts = ksplit >= kGramParts ? kGramParts : 1;
+    const long blocks = (count * parts + kGfThreads - 1) / kGfThreads;
+    if (parts > 1)
+        hipLaunchKernelGGL(k_gram_finalize<kGramParts>, dim3((unsigned)blocks),
+                           dim3(kGfThreads), 0, st, part, ns, count, ksplit,
+                           h3, out);
+    else
+        hipLaunchKernelGGL(k_gram_finalize<1>, dim3((unsigned)blocks),
+                           dim3(kGfThreads), 0, st, part, ns, count, ksplit,
+                           h3, out);
     return hipGetLastError();
 }
 
