@@ -637,12 +637,15 @@ void layout(ks_grid *g)
     // Gram: split the grid so that about 1024 workgroups share the work
     // (gram_tile x gram_tile state tiles on and above the diagonal, per
     // k-point; each slice leaves a partial matrix), each slice at least 512
-    // points
+    // points, or 256 where those would leave fewer than two workgroups per
+    // CU (12^3 points x 500 states: 36 tiles, 3 slices 183 us, 6 104 us)
     {
         const long nt = (g->ns + gram_tile(g->ns) - 1) / gram_tile(g->ns);
         const long tiles = nt * (nt + 1) / 2 * g->nk;
         const long want = std::max<long>(1, (1024 + tiles - 1) / tiles);
-        const long most = std::max<long>(1, (long)N / 512);
+        long most = (long)N / 512;
+        if (most * tiles < 512)
+            most = (long)N / 256;
         g->gram_ksplit = (int)std::max<long>(1, std::min(want, most));
     }
     g->lay.gpart = take((size_t)g->gram_ksplit * g->nk * g->ns * g->ns * 16);
