@@ -9,8 +9,11 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
+#include <cstdint>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <tuple>
 #include <cstdarg>
@@ -79,8 +82,10 @@ struct ks_grid {
     // launch shape
     int TY = 1, zchunk = 1, ntile_y = 1, nzc = 1, rpt = 1;
     bool auto_shape = false;    // the library's choice (no caller's shape)
-    // its choice for H.psi calls on the states of one k-point
-    int call_TY = 0, call_zchunk = 0, call_rpt = 0;
+    // its choices for H.psi calls on 1 .. ns states, at the number of states,
+    // and at 0 for the current, as they are first asked for (packed, 0: not
+    // yet); they depend on nothing that changes after creation
+    std::unique_ptr<std::atomic<uint64_t>[]> shapes;
 
     // device bytes of the tables allocated by dev_alloc
     size_t owned_bytes = 0;
@@ -442,6 +447,15 @@ struct Shape {
     int TY = 0, zchunk = 0, rpt = 0;
 };
 
+// The next smaller of the values ceil(n / i) after p (0 after 1).
+int next_part(int n, int p)
+{
+    if (p <= 1)
+        return 0;
+    const int i = (n + p - 2) / (p - 1);   // the first i with a smaller one
+    return (n + i - 1) / i;
+}
+
 // The launch shape for ns states: the one with the least modelled time.  A
 // workgroup of w wavefronts takes a fixed start (tables, first planes: 2.5
 // us) and a time per plane that grows with the wavefronts resident on its CU;
@@ -480,22 +494,17 @@ Shape pick_shape(const ks_grid *g, int ns, int rpt_only = 0)
             pb = 0.052;
             pc = 0.0;
         }
-        for (int nt = 1, last = 0; nt <= G.ny; ++nt) {
-            const int TY = (G.ny + nt - 1) / nt;
-            if (TY == last || TY < rpt || !tile_ok(g, TY, rpt))
+        // (tile heights and chunks: every ceil(n / i) once, from the tallest)
+        for (int TY = G.ny; TY >= rpt; TY = next_part(G.ny, TY)) {
+            if (!tile_ok(g, TY, rpt))
                 continue;
-            last = TY;
             const int nthr = hpsi_threads(G.nx, TY, rpt);
             const int w = nthr / 64;
             const int ntile = (G.ny + TY - 1) / TY;
             const double halo = 1.0 + 0.1 * (8.0 / TY - 0.5);
             const bool spills = !mx && rpt == 2 &&
                                 hpsi_halo_per_thread(G, TY, nthr) > 2;
-            for (int nz = 1, lastz = 0; nz <= G.nz; ++nz) {
-                const int zc = (G.nz + nz - 1) / nz;
-                if (zc == lastz)
-                    continue;
-                lastz = zc;
+            for (int zc = G.nz; zc >= 1; zc = next_part(G.nz, zc)) {
                 const size_t lds =
                     rpt_only > 0 ? hpsi_lds_bytes(G.nx, TY, zc, false)
                                  : lds_for(g, TY, zc);
@@ -534,6 +543,28 @@ Shape pick_shape(const ks_grid *g, int ns, int rpt_only = 0)
     return best;
 }
 
+// The same for a call on ns of a k-point's states (ns = 0: the current's),
+// searched for once: the search takes the host 2 to 50 us, where the smallest
+// call takes 17.
+Shape kept_shape(const ks_grid *g, int ns)
+{
+    constexpr uint64_t kDone = 1ull << 63;
+    std::atomic<uint64_t> &slot = g->shapes[ns];
+    uint64_t v = slot.load(std::memory_order_relaxed);
+    if (!v) {
+        const Shape s = ns > 0 ? pick_shape(g, ns)
+                               : pick_shape(g, g->stot, 1);
+        v = kDone | (uint64_t)s.rpt << 48 | (uint64_t)s.TY << 32 |
+            (uint32_t)s.zchunk;
+        slot.store(v, std::memory_order_relaxed);
+    }
+    Shape s;
+    s.rpt = (int)(v >> 48 & 3);
+    s.TY = (int)(v >> 32 & 0xffff);
+    s.zchunk = (int)(uint32_t)v;
+    return s;
+}
+
 int set_tiles(ks_grid *g, int TY, int zchunk, int rpt)
 {
     const Geo &G = g->geo;
@@ -543,10 +574,6 @@ int set_tiles(ks_grid *g, int TY, int zchunk, int rpt)
         TY = s.TY;
         zchunk = s.zchunk;
         rpt = s.rpt;
-        const Shape c = pick_shape(g, g->ns);
-        g->call_TY = c.TY;
-        g->call_zchunk = c.zchunk;
-        g->call_rpt = c.rpt;
     }
     const bool auto_rpt = rpt <= 0, auto_ty = TY <= 0;
     if (auto_rpt)
@@ -780,14 +807,7 @@ void call_shape(const ks_grid *g, int ns, HArgs *a)
 {
     if (!g->auto_shape || ns <= 0)
         return;
-    Shape s;
-    if (ns == g->ns) {
-        s.TY = g->call_TY;
-        s.zchunk = g->call_zchunk;
-        s.rpt = g->call_rpt;
-    } else {
-        s = pick_shape(g, ns);
-    }
+    const Shape s = kept_shape(g, ns);
     if (s.TY > 0)
         use_shape(g, s, a);
 }
@@ -1194,6 +1214,7 @@ int ks_grid_create(const ks_grid_desc *d, ks_grid **out)
         ks_grid_destroy(g);
         return rc;
     }
+    g->shapes.reset(new std::atomic<uint64_t>[g->ns + 1]());
     if ((rc = set_tiles(g, 0, 0, 0))) {
         ks_grid_destroy(g);
         return rc;
@@ -1361,7 +1382,7 @@ int ks_current(ks_grid *g, const void *d_psi, double t, double out_host[3])
         return rc;
     // stencil part: the H.psi kernel's tiles (one row per thread), each
     // writing its three partial sums
-    const Shape sh = pick_shape(g, g->stot, 1);
+    const Shape sh = kept_shape(g, 0);
     if (sh.TY < 1)
         return fail(KS_E_UNSUPPORTED, "no tile shape for the current");
     HArgs h = base_hargs(g);
