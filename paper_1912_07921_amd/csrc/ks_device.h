@@ -759,10 +759,11 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
     };
     auto kb_ld = [&](int r, int zq) -> V {
         unsigned off = kBufNone;
-        // (the second row of an item of one row per thread in a launch of
-        // two would be past the tile, and in its last plane past the table)
-        if (proj && (r == 0 || r < rpt) && zq >= z0 && zq < z1) {
-            const int2 ri = sRow[(zq - z0) * TY + row0 + r];
+        if (proj && zq >= z0 && zq < z1) {
+            // (an item of one row per thread in a launch of two has no
+            // second row: past the tile, in its last plane past the table)
+            const int2 ri =
+                sRow[(zq - z0) * TY + row0 + min(r, rpt - 1)];
             const unsigned d = (unsigned)x - (unsigned)(ri.x & 0xffff);
             if (valid[r] && d <= (unsigned)ri.x >> 16)
                 off = (unsigned)(ri.y + x) * (unsigned)sizeof(V);
