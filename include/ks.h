@@ -342,10 +342,12 @@ int ks_autotune(ks_grid *g, const void *d_psi, int reps, int out_shape[3],
  * (with one batched projector gather and apply), the density / potential /
  * dipole / norm reductions of all jobs as one launch each, and one ETRS
  * step (the same step as ks_propagate_etrs) is captured once as a HIP graph
- * and replayed.  Results
- * equal those of ks_propagate_etrs on each job alone, for the same launch
- * shapes.  Grids must share the precision, have a workspace, and not be used
- * on their own while the batch exists (the batch sets their stream). */
+ * and replayed.  A grid in the library's launch shape runs in a shape chosen
+ * for the batch's total work, one in a caller's shape (ks_set_launch,
+ * ks_autotune) in that; the norms keep the partial sums of the grid's own
+ * shape.  Results equal those of ks_propagate_etrs on each job alone.  Grids
+ * must share the precision, have a workspace, and not be used on their own
+ * while the batch exists (the batch sets their stream). */
 typedef struct ks_batch ks_batch;
 
 typedef struct {

@@ -456,44 +456,69 @@ int next_part(int n, int p)
     return (n + i - 1) / i;
 }
 
-// The launch shape for ns states: the one with the least modelled time.  A
-// workgroup of w wavefronts takes a fixed start (tables, first planes: 2.5
-// us) and a time per plane that grows with the wavefronts resident on its CU;
-// the launch takes that for every round of workgroups over the 256 CUs.  A
-// chunk of zc planes marches zc + 4 (the last four only complete outputs).
-// The constants are fits to one pass on MI355X (us per plane at 3 / 5 / 8 /
-// 12 resident wavefronts: FP64 0.6 / 0.8 / 1.05 / 1.6 with one row per thread,
-// - / 1.35 / 1.9 / - with two; FP32 0.58 / 0.68 / 0.8 / - and 1.1 / 1.1 / 1.25
-// / -), the halo term the difference of 8 and 16-row tiles at 64^3.  Few states and
-// small grids thus get short chunks of low tiles (24^3 x 4 states, 4 -> 192
-// workgroups: 40 -> 6 us per pass), large ones tall tiles of the whole axis.
-// rpt_only > 0 restricts the rows per thread (the current's kernel has one).
-Shape pick_shape(const ks_grid *g, int ns, int rpt_only = 0)
+// The launch-shape model.  A workgroup of w wavefronts takes a fixed start
+// (tables, first planes: 2.5 us) and a time per plane that grows with the
+// wavefronts resident on its CU; a launch takes that for every round of
+// workgroups over the 256 CUs.  A chunk of zc planes marches zc + 4 (the last
+// four only complete outputs).  The constants are fits to one pass on MI355X
+// (us per plane at 3 / 5 / 8 / 12 resident wavefronts: FP64 0.6 / 0.8 / 1.05 /
+// 1.6 with one row per thread, - / 1.35 / 1.9 / - with two; FP32 0.58 / 0.68 /
+// 0.8 / - and 1.1 / 1.1 / 1.25 / -), the halo term the difference of 8 and
+// 16-row tiles at 64^3.
+constexpr int kCUs = 256;
+constexpr double kStartUs = 2.5;
+
+// Time per plane of a tile of TY rows in workgroups of nthr threads, beside
+// wr resident wavefronts in all.  current: the current's kernel (FP64, one row
+// per thread).
+double plane_us(const ks_grid *g, int TY, int rpt, int nthr, double wr,
+                bool current = false)
 {
     const Geo &G = g->geo;
-    const bool mx = g->mixed && rpt_only == 0;
-    constexpr int kCUs = 256;
+    const bool mx = g->mixed && !current;
+    // a + b w + c w^2 (two rows per thread on a periodic grid: 0.2 us more
+    // for the wrapped columns)
+    const bool per = G.per[0] || G.per[1] || G.per[2];
+    double pa = 0.42, pb = 0.05, pc = 0.004;
+    if (current) {
+        pb = 0.08;
+        pc = 0.0;
+    } else if (rpt == 2) {
+        pa = mx ? 0.85 : (per ? 0.70 : 0.50);
+        pb = mx ? 0.05 : 0.17;
+        pc = 0.0;
+    } else if (mx) {
+        pa = 0.45;
+        pb = 0.052;
+        pc = 0.0;
+    }
+    const double halo = 1.0 + 0.1 * (8.0 / TY - 0.5);
+    const bool spills = !mx && rpt == 2 &&
+                        hpsi_halo_per_thread(G, TY, nthr) > 2;
+    return (pa + pb * wr + pc * wr * wr) * halo * (spills ? 1.3 : 1.0);
+}
+
+// Workgroups of w wavefronts and lds bytes that a CU holds: by registers four
+// or three wavefronts per SIMD with one row per thread (FP32, FP64), two with
+// two (and the current's); a workgroup takes ceil(w / 4) of every SIMD's.
+int cu_fit(bool mixed, int rpt, int w, size_t lds, bool current = false)
+{
+    const int room = rpt == 2 || current ? 8 : (mixed ? 16 : 12);
+    return std::max(1, std::min(room / 4 / ((w + 3) / 4),
+                                (int)(kLdsBudget / lds)));
+}
+
+// The launch shape for ns states: the one with the least modelled time.  Few
+// states and small grids thus get short chunks of low tiles (24^3 x 4 states, 4
+// -> 240 workgroups: 40 -> 6 us per pass), large ones tall tiles of the whole
+// axis.  current: for the current's kernel (one row per thread, no projector
+// table).
+Shape pick_shape(const ks_grid *g, int ns, bool current = false)
+{
+    const Geo &G = g->geo;
     Shape best;
     double t_best = 1e300;
-    for (int rpt = 1; rpt <= 2; ++rpt) {
-        if (rpt_only > 0 && rpt != rpt_only)
-            continue;
-        // time per plane a + b w + c w^2 at w resident wavefronts (two rows
-        // per thread on a periodic grid: 0.2 us more for the wrapped columns)
-        const bool per = G.per[0] || G.per[1] || G.per[2];
-        double pa = 0.42, pb = 0.05, pc = 0.004;
-        if (rpt_only > 0) {
-            pb = 0.08;
-            pc = 0.0;
-        } else if (rpt == 2) {
-            pa = mx ? 0.85 : (per ? 0.70 : 0.50);
-            pb = mx ? 0.05 : 0.17;
-            pc = 0.0;
-        } else if (mx) {
-            pa = 0.45;
-            pb = 0.052;
-            pc = 0.0;
-        }
+    for (int rpt = 1; rpt <= (current ? 1 : 2); ++rpt) {
         // (tile heights and chunks: every ceil(n / i) once, from the tallest)
         for (int TY = G.ny; TY >= rpt; TY = next_part(G.ny, TY)) {
             if (!tile_ok(g, TY, rpt))
@@ -501,32 +526,23 @@ Shape pick_shape(const ks_grid *g, int ns, int rpt_only = 0)
             const int nthr = hpsi_threads(G.nx, TY, rpt);
             const int w = nthr / 64;
             const int ntile = (G.ny + TY - 1) / TY;
-            const double halo = 1.0 + 0.1 * (8.0 / TY - 0.5);
-            const bool spills = !mx && rpt == 2 &&
-                                hpsi_halo_per_thread(G, TY, nthr) > 2;
             for (int zc = G.nz; zc >= 1; zc = next_part(G.nz, zc)) {
                 const size_t lds =
-                    rpt_only > 0 ? hpsi_lds_bytes(G.nx, TY, zc, false)
-                                 : lds_for(g, TY, zc);
+                    current ? hpsi_lds_bytes(G.nx, TY, zc, false)
+                            : lds_for(g, TY, zc);
                 if (lds > kLdsBudget)
                     continue;
                 const long nwg = (long)ntile * ((G.nz + zc - 1) / zc) * ns;
-                // wavefronts a CU holds (registers): four or three per SIMD
-                // with one row per thread (FP32, FP64), two with two
-                // (and the current's)
-                const int room =
-                    rpt == 2 || rpt_only > 0 ? 8 : (mx ? 16 : 12);
-                // (a workgroup takes ceil(w / 4) of every SIMD's)
-                const int fit = std::max(
-                    1, std::min(room / 4 / ((w + 3) / 4),
-                                (int)(kLdsBudget / lds)));
+                const int fit = cu_fit(g->mixed && !current, rpt, w, lds,
+                                       current);
                 const long per_cu = std::min<long>(
                     fit, (nwg + kCUs - 1) / kCUs);
                 const long rounds = (nwg + kCUs * fit - 1) / (kCUs * fit);
-                const double wr = (double)(per_cu * w);
-                const double plane = (pa + pb * wr + pc * wr * wr) * halo *
-                                     (spills ? 1.3 : 1.0);
-                const double t = rounds * (2.5 + (zc + 4) * plane);
+                const double t =
+                    rounds * (kStartUs +
+                              (zc + 4) * plane_us(g, TY, rpt, nthr,
+                                                  (double)(per_cu * w),
+                                                  current));
                 if (t < t_best) {
                     t_best = t;
                     best.TY = TY;
@@ -553,7 +569,7 @@ Shape kept_shape(const ks_grid *g, int ns)
     uint64_t v = slot.load(std::memory_order_relaxed);
     if (!v) {
         const Shape s = ns > 0 ? pick_shape(g, ns)
-                               : pick_shape(g, g->stot, 1);
+                               : pick_shape(g, g->stot, true);
         v = kDone | (uint64_t)s.rpt << 48 | (uint64_t)s.TY << 32 |
             (uint32_t)s.zchunk;
         slot.store(v, std::memory_order_relaxed);
@@ -2219,6 +2235,10 @@ struct ks_batch {
     DipJob *d_dip = nullptr;
     NormJob *d_norm = nullptr;
     int ndip = 0, nnorm = 0, max_ns = 0;
+    // norm partials of the jobs whose launch shape is the batch's choice
+    NormTiles *d_ntile = nullptr;
+    int *d_ntile_off = nullptr;
+    int nntile = 0, blk_ntile = 0, nthr_ntile = 64;
     std::vector<int> steps_done;
     bool use_graph = true;
     hipGraph_t graph = nullptr;
@@ -2290,6 +2310,100 @@ int batch_poll_flags(ks_batch *b, bool wait)
     return KS_OK;
 }
 
+// Launch shapes of a batch's jobs.  A grid's own choice fills the chip with
+// that grid alone; among other jobs its short chunks and low tiles only re-read
+// planes and rows, and its last round meets other jobs' workgroups.  Unless the
+// model finds them faster all the same, the jobs whose grids hold the library's
+// choice take one row per thread, the tallest tile of 512 threads and chunks of
+// the whole, half or a third of the axis, or the tallest of 256 and halves; a
+// caller's shape stays.  The launch is taken to last its work over the
+// workgroups that the CUs hold at once (all as large as the largest) plus 0.4
+// of its longest workgroup.  Of twelve such rules timed on 34 batches (2 to 40
+// jobs, 24^3 to 80^3, both precisions) this choice is within 11 % of the best,
+// 2 % on average.  us a step, own shapes -> these: FP64 16 jobs of 24^3 x 16
+// states 1607 -> 900, 16 of 64^3 x 4 2729 -> 2118, 8 of mixed sizes 1972 ->
+// 1710 (mixed precision 1086 -> 836, 2175 -> 1630, 1564 -> 1282); 4 of 64^3 x
+// 32 keep their own.
+// `apart`: the norms of jobs in another shape than their own are summed apart
+// (3 % of a step).
+void batch_shapes(const std::vector<ks_grid *> &grids, bool apart,
+                  std::vector<Shape> *out)
+{
+    struct Rule {
+        int threads, chunks;     // 0: the grids' own shapes
+    };
+    double best = 1e300;
+    for (const Rule r : {Rule{0, 0}, Rule{512, 1}, Rule{512, 2}, Rule{512, 3},
+                         Rule{256, 2}}) {
+        std::vector<Shape> v;
+        int rpt = 1, nthr = 64;
+        size_t lds = 1;
+        bool own = true;
+        for (const ks_grid *g : grids) {
+            const Geo &G = g->geo;
+            Shape s;
+            s.TY = g->TY;
+            s.zchunk = g->zchunk;
+            s.rpt = g->rpt;
+            if (r.chunks > 0 && g->auto_shape) {
+                const int zc = (G.nz + r.chunks - 1) / r.chunks;
+                int TY = std::max(1, std::min(G.ny, r.threads / G.nx));
+                while (TY > 0 && !(tile_ok(g, TY, 1) &&
+                                   lds_for(g, TY, zc) <= kLdsBudget))
+                    --TY;
+                if (TY > 0) {
+                    own = own && TY == s.TY && zc == s.zchunk && s.rpt == 1;
+                    s.TY = TY;
+                    s.zchunk = zc;
+                    s.rpt = 1;
+                }
+            }
+            rpt = std::max(rpt, s.rpt);
+            nthr = std::max(nthr, hpsi_threads(G.nx, s.TY, s.rpt));
+            lds = std::max(lds, lds_for(g, s.TY, s.zchunk));
+            v.push_back(s);
+        }
+        const int fit = cu_fit(grids[0]->mixed, rpt, nthr / 64, lds);
+        // workgroups, and their mean of wavefronts at work
+        double nwg = 0.0, waves = 0.0;
+        std::vector<double> n, w;
+        for (size_t i = 0; i < v.size(); ++i) {
+            const Geo &G = grids[i]->geo;
+            const Shape &s = v[i];
+            n.push_back((double)((G.ny + s.TY - 1) / s.TY) *
+                        ((G.nz + s.zchunk - 1) / s.zchunk) * grids[i]->stot);
+            w.push_back(G.nx * ((s.TY + s.rpt - 1) / s.rpt) / 64.0);
+            nwg += n[i];
+            waves += n[i] * w[i];
+        }
+        const double held = std::min((double)fit, std::ceil(nwg / kCUs));
+        double sum = 0.0, longest = 0.0;
+        for (size_t i = 0; i < v.size(); ++i) {
+            const Shape &s = v[i];
+            const double t =
+                kStartUs + (s.zchunk + 4) *
+                               plane_us(grids[i], s.TY, s.rpt, nthr,
+                                        w[i] + (held - 1.0) * waves / nwg);
+            sum += n[i] * t;
+            longest = std::max(longest, t);
+        }
+        double t = nwg <= kCUs * fit ? longest
+                                     : sum / (kCUs * fit) + 0.4 * longest;
+        if (apart && !own)
+            t *= 1.03;
+        if (t < best) {
+            best = t;
+            *out = v;
+        }
+    }
+}
+
+// Whether the partials of a job's norms are summed apart from its final pass.
+bool norms_apart(const ks_grid *g, const HArgs &h)
+{
+    return h.TY != g->TY || h.zchunk != g->zchunk || h.rpt != g->rpt;
+}
+
 // Enqueue one ETRS step of every job on the batch stream.
 int batch_enqueue_step(ks_batch *b)
 {
@@ -2334,6 +2448,8 @@ int batch_enqueue_step(ks_batch *b)
                                   st));
     }
     KS_HIP(launch_dipole_finalize_batch(b->d_dip, b->ndip, st));
+    KS_HIP(launch_norm_tiles_batch(b->d_ntile, b->d_ntile_off, b->nntile,
+                                   b->blk_ntile, b->nthr_ntile, st));
     KS_HIP(launch_norm_finalize_batch(b->d_norm, b->nnorm, b->max_ns, st));
     KS_HIP(launch_step_advance(b->d_steps, (int)b->grids.size(), st));
     return KS_OK;
@@ -2381,12 +2497,19 @@ int ks_batch_create(const ks_job *jobs, int njobs, void *stream,
     b->mixed = mixed;
     b->jobs.assign(jobs, jobs + njobs);
     b->hm = 2;
+    for (int i = 0; i < njobs; ++i)
+        b->grids.push_back(jobs[i].grid);
+    bool norms = false;
+    for (int i = 0; i < njobs; ++i)
+        norms = norms || jobs[i].d_norms;
+    std::vector<Shape> shapes;
+    batch_shapes(b->grids, norms, &shapes);
     for (int i = 0; i < njobs; ++i) {
         ks_grid *g = jobs[i].grid;
         g->stream = b->stream;
-        b->grids.push_back(g);
         JobDev J;
         J.h = base_hargs(g);
+        use_shape(g, shapes[i], &J.h);
         J.g = base_gargs(g);
         J.g.D = g->ws + g->lay.D;
         J.g.ns = g->stot;
@@ -2399,8 +2522,9 @@ int ks_batch_create(const ks_job *jobs, int njobs, void *stream,
         J.t[2] = g->ws + g->lay.t3;
         J.npart = wsp<double>(g, g->lay.npart);
         J.npart_end = (g->nonlin || jobs[i].d_dipole) ? 1 : 0;
-        J.normpart_end = jobs[i].d_norms ? wsp<double>(g, g->lay.normpart)
-                                         : nullptr;
+        J.normpart_end = jobs[i].d_norms && !norms_apart(g, J.h)
+                             ? wsp<double>(g, g->lay.normpart)
+                             : nullptr;
         J.vion = jobs[i].d_vion;
         J.vcur = g->d_v;
         J.vpred = wsp<double>(g, g->lay.vpred);
@@ -2410,14 +2534,26 @@ int ks_batch_create(const ks_job *jobs, int njobs, void *stream,
         b->hjobs.push_back(J);
         if (g->laser[0] != 0.0)
             b->grad = true;
-        b->rpt = std::max(b->rpt, g->rpt);
-        b->nthr = std::max(b->nthr, hpsi_threads(g->geo.nx, g->TY, g->rpt));
-        b->lds = std::max(b->lds, lds_for(g, g->TY, g->zchunk));
+        b->rpt = std::max(b->rpt, J.h.rpt);
+        b->nthr = std::max(b->nthr,
+                           hpsi_threads(g->geo.nx, J.h.TY, J.h.rpt));
+        b->lds = std::max(b->lds, lds_for(g, J.h.TY, J.h.zchunk));
     }
     // halo loads per thread for the workgroup size of the batch (the
-    // largest any job asks for)
-    for (ks_grid *g : b->grids)
-        b->hm = std::max(b->hm, hpsi_halo_per_thread(g->geo, g->TY, b->nthr));
+    // largest any job asks for; more threads where two rows per thread
+    // allow no more loads)
+    auto halo = [&]() {
+        b->hm = 2;
+        for (int i = 0; i < njobs; ++i)
+            b->hm = std::max(b->hm, hpsi_halo_per_thread(b->grids[i]->geo,
+                                                         shapes[i].TY,
+                                                         b->nthr));
+    };
+    halo();
+    if (b->rpt == 2 && b->hm > 8) {
+        b->nthr = kRowThreads;
+        halo();
+    }
     if (b->rpt == 2 && b->hm > 8) {
         ks_batch_destroy(b);
         return fail(KS_E_UNSUPPORTED, "batch halo too large for two-row "
@@ -2504,7 +2640,7 @@ int ks_batch_create(const ks_job *jobs, int njobs, void *stream,
             a.v = e == 0 ? J.vcur : (J.nonlin ? J.vpred : J.vion);
             a.v32 = mixed ? wsp<float>(b->grids[i], b->grids[i]->lay.v32)
                           : nullptr;
-                a.cim = -0.5 * J.dt / j;
+            a.cim = -0.5 * J.dt / j;
             if (j < 4) {
                 a.out = J.t[j - 1];
             } else {
@@ -2575,6 +2711,9 @@ int ks_batch_create(const ks_job *jobs, int njobs, void *stream,
         std::vector<int> opred(1, 0), oend(1, 0);
         std::vector<DipJob> dip;
         std::vector<NormJob> nrm;
+        std::vector<NormTiles> ntl;
+        std::vector<int> ontl(1, 0);
+        long blk_ntl = 0;
         for (int i = 0; i < njobs; ++i) {
             ks_grid *g = b->grids[i];
             const ks_job &jb = b->jobs[i];
@@ -2620,9 +2759,29 @@ int ks_batch_create(const ks_job *jobs, int njobs, void *stream,
                 n.flag = b->d_flags + i;
                 nrm.push_back(n);
                 b->max_ns = std::max(b->max_ns, g->stot);
+                if (!b->hjobs[i].normpart_end) {
+                    NormTiles t;
+                    t.psi = b->hjobs[i].psi;
+                    t.part = wsp<double>(g, g->lay.normpart);
+                    t.nx = g->geo.nx;
+                    t.ny = g->geo.ny;
+                    t.nz = g->geo.nz;
+                    t.TY = g->TY;
+                    t.rpt = g->rpt;
+                    t.zchunk = g->zchunk;
+                    t.ntile_y = g->ntile_y;
+                    t.nzc = g->nzc;
+                    ntl.push_back(t);
+                    blk_ntl += (long)n.ntiles * g->stot;
+                    ontl.push_back((int)std::min(blk_ntl, (1L << 31) - 1));
+                    b->nthr_ntile = std::max(
+                        b->nthr_ntile,
+                        hpsi_threads(g->geo.nx, g->TY, g->rpt));
+                }
             }
         }
-        if ((long)opred.back() + oend.back() >= (1L << 31)) {
+        if ((long)opred.back() + oend.back() >= (1L << 31) ||
+            blk_ntl >= (1L << 31)) {
             ks_batch_destroy(b);
             return fail(KS_E_UNSUPPORTED, "batch densities too large");
         }
@@ -2630,6 +2789,8 @@ int ks_batch_create(const ks_job *jobs, int njobs, void *stream,
         b->nend = (int)dend.size();
         b->blk_pred = opred.back();
         b->blk_end = oend.back();
+        b->nntile = (int)ntl.size();
+        b->blk_ntile = ontl.back();
         b->ndip = (int)dip.size();
         b->nnorm = (int)nrm.size();
         auto put = [&](auto **dst, const auto &v) -> int {
@@ -2645,7 +2806,9 @@ int ks_batch_create(const ks_job *jobs, int njobs, void *stream,
         if ((rc = put(&b->d_dpred, dpred)) ||
             (rc = put(&b->d_dpred_off, opred)) ||
             (rc = put(&b->d_dend, dend)) || (rc = put(&b->d_dend_off, oend)) ||
-            (rc = put(&b->d_dip, dip)) || (rc = put(&b->d_norm, nrm))) {
+            (rc = put(&b->d_dip, dip)) || (rc = put(&b->d_norm, nrm)) ||
+            (rc = put(&b->d_ntile, ntl)) ||
+            (rc = put(&b->d_ntile_off, ontl))) {
             ks_batch_destroy(b);
             return rc;
         }

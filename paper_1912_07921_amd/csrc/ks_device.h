@@ -120,6 +120,11 @@ template <class V> __device__ __forceinline__ V cmulf(V a, V b)
     r.y = rfma(a.y, b.x, a.x * b.y);
     return r;
 }
+// |a|^2 with its roundings fixed
+__device__ __forceinline__ double abs2f(double re, double im)
+{
+    return rfma(im, im, re * re);
+}
 // A copy the optimiser cannot trace: what is computed from it inside a loop
 // stays in the loop (the LDS addresses of the H.psi kernel would otherwise be
 // hoisted into tens of vector registers and spill).
@@ -1105,7 +1110,7 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
                                           8.0 * t3.y + 16.0 * (double)t4.y;
                         part = w_occ * (pr * pr + pi * pi);
                     } else {
-                        const double sq = re * re + im * im;
+                        const double sq = abs2f(re, im);
                         part = w_occ * sq;
                         if (act[r] && emit)
                             nrm += sq;

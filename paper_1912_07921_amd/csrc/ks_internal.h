@@ -235,7 +235,18 @@ struct NormJob {
     const int *step = nullptr;
     int *flag = nullptr;             // set to 1 (sticky) by a NaN / Inf norm
 };
+// The norm partials of a job whose final pass ran in another launch shape than
+// its grid's: the same sums of the grid's own tiles.
+struct NormTiles {
+    const double2 *psi = nullptr;
+    double *part = nullptr;          // [ns][ntile_y * nzc]
+    int nx = 1, ny = 1, nz = 1, TY = 1, rpt = 1, zchunk = 1, ntile_y = 1,
+        nzc = 1;
+};
 // blk_off[j] = first launch block of job j (blk_off[njobs] = nblocks)
+hipError_t launch_norm_tiles_batch(const NormTiles *jobs, const int *blk_off,
+                                   int njobs, int nblocks, int nthr,
+                                   hipStream_t st);
 hipError_t launch_density_batch(const DArgs *args, const int *blk_off,
                                 int njobs, int nblocks, hipStream_t st);
 hipError_t launch_dipole_finalize_batch(const DipJob *jobs, int njobs,

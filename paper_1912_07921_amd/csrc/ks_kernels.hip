@@ -258,6 +258,49 @@ __global__ __launch_bounds__(64) void k_norm_finalize_batch(
                         blockIdx.x, sbuf, J.flag);
 }
 
+// The norm partials of the tiles a grid's own H.psi launches take: a
+// workgroup sums a tile with the threads, rows and planes in the order of the
+// final pass (hpsi_item), so that partials and norms have the same bits
+// whatever shape a batch runs.  One read of the states, after eight passes.
+__global__ __launch_bounds__(512) void k_norm_tiles_batch(
+    const NormTiles *jobs, const int *blk_off, int njobs)
+{
+    __shared__ double sbuf[8];
+    int j = 0;
+    for (int b = blockIdx.x; b < blk_off[njobs]; b += gridDim.x) {
+        while (b >= blk_off[j + 1])
+            ++j;
+        const NormTiles J = jobs[j];
+        const int ntiles = J.ntile_y * J.nzc;
+        const int w = b - blk_off[j];
+        const int sl = w / ntiles, tile = w - sl * ntiles;
+        const int zc = tile / J.ntile_y, y0 = (tile - zc * J.ntile_y) * J.TY;
+        const int rpt = min(J.rpt, J.TY);
+        const int rows = min(J.TY, J.ny - y0);
+        const int x = threadIdx.x % J.nx, yl = threadIdx.x / J.nx;
+        const int row0 = min(yl * rpt, J.TY - rpt);
+        const long P = (long)J.nx * J.ny;
+        const int z0 = zc * J.zchunk, z1 = min(J.nz, z0 + J.zchunk);
+        double acc[1] = {0.0};
+        if (yl < (J.TY + rpt - 1) / rpt) {
+            // this thread's rows that no lower thread counts
+            const int r0 = yl * rpt - row0, r1 = min(rpt, rows - row0);
+            const double2 *p = J.psi + ((size_t)sl * J.nz + z0) * P +
+                               (long)(y0 + row0) * J.nx + x;
+#pragma unroll 4
+            for (int z = z0; z < z1; ++z, p += P)
+                for (int r = r0; r < r1; ++r) {
+                    const double2 v = gld(p + r * J.nx);
+                    acc[0] += abs2f(v.x, v.y);
+                }
+        }
+        block_sum<double, 1>(acc, sbuf);
+        if (threadIdx.x == 0)
+            J.part[(size_t)sl * ntiles + tile] = acc[0];
+        __syncthreads();
+    }
+}
+
 // psi <- exp(i kappa z) psi
 __global__ __launch_bounds__(256) void k_kick(Geo G, double2 *psi,
                                               double kappa)
@@ -746,6 +789,18 @@ hipError_t launch_norm_finalize_batch(const NormJob *jobs, int njobs,
         return hipSuccess;
     hipLaunchKernelGGL(k_norm_finalize_batch, dim3(max_ns, njobs), dim3(64), 0,
                        st, jobs);
+    return hipGetLastError();
+}
+
+hipError_t launch_norm_tiles_batch(const NormTiles *jobs, const int *blk_off,
+                                   int njobs, int nblocks, int nthr,
+                                   hipStream_t st)
+{
+    if (njobs <= 0 || nblocks <= 0)
+        return hipSuccess;
+    // (2^22 workgroups of 512 threads at most)
+    hipLaunchKernelGGL(k_norm_tiles_batch, dim3(std::min(nblocks, 1 << 22)),
+                       dim3(nthr), 0, st, jobs, blk_off, njobs);
     return hipGetLastError();
 }
 
