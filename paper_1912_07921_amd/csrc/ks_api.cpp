@@ -459,28 +459,54 @@ int next_part(int n, int p)
 // The launch-shape model.  A workgroup of w wavefronts takes a fixed start
 // (tables, first planes: 2.5 us) and a time per plane that grows with the
 // wavefronts resident on its CU; a launch takes that for every round of
-// workgroups over the 256 CUs.  A chunk of zc planes marches zc + 4 (the last
-// four only complete outputs).  The constants are fits to one pass on MI355X
-// (us per plane at 3 / 5 / 8 / 12 resident wavefronts: FP64 0.6 / 0.8 / 1.05 /
-// 1.6 with one row per thread, - / 1.35 / 1.9 / - with two; FP32 0.58 / 0.68 /
-// 0.8 / - and 1.1 / 1.1 / 1.25 / -), the halo term the difference of 8 and
-// 16-row tiles at 64^3.
+// workgroups over the 256 CUs.  A chunk of zc planes costs zc + 4: the FP64
+// kernel marches four more, which only complete outputs, the FP32 kernel zc,
+// but starts with the loads of nine (charged 0 to 3 planes for them, it gets
+// short chunks of two rows per thread, which take up to 13 % longer).  The
+// constants are fits to one pass on MI355X (us per plane at 3 / 5 / 8 / 12
+// resident wavefronts: FP64 0.6 / 0.8 / 1.05 / 1.6 with one row per thread, - /
+// 1.35 / 1.9 / - with two; FP32 0.58 / 0.68 / 0.8 / - and 1.1 / 1.1 / 1.25 /
+// -), the halo term the difference of 8 and 16-row tiles at 64^3.  FP32 steps on
+// periodic grids have their own for one row per thread (0.55 + 0.02 a
+// wavefront, three planes): their large launches are bound by the halo rows,
+// all of them loaded, whatever the wavefronts.  With the finite grid's, 48^3 x
+// 256 states took 8-row tiles, 260 us a pass, where 10 rows take 221, and a
+// slab of 60 x 50 x 90 x 40 two rows per thread, 107 where one takes 97.
+// Over 15 grids (24^3 to 128^3, finite, periodic, slab, 8 to 256 states) and
+// some 30 shapes of each the choice is within 16 % of the fastest pass in FP64
+// (24^3 periodic; 6 % elsewhere) and 9 % in FP32, 2 % on average in either.
 constexpr int kCUs = 256;
 constexpr double kStartUs = 2.5;
 
+// What a shape is for: the passes of a step, one H.psi call (FP64 in and out
+// in either precision), the current (FP64, one row per thread).
+enum class Use { steps, call, current };
+
+// FP32 passes of steps on a periodic grid (above)
+bool fp32_periodic(const ks_grid *g, Use use)
+{
+    return g->mixed && use == Use::steps &&
+           (g->geo.per[0] || g->geo.per[1] || g->geo.per[2]);
+}
+
+// Planes a chunk costs beside its own.
+int extra_planes(const ks_grid *g, int rpt, Use use)
+{
+    return fp32_periodic(g, use) && rpt == 1 ? 3 : 4;
+}
+
 // Time per plane of a tile of TY rows in workgroups of nthr threads, beside
-// wr resident wavefronts in all.  current: the current's kernel (FP64, one row
-// per thread).
+// wr resident wavefronts in all.
 double plane_us(const ks_grid *g, int TY, int rpt, int nthr, double wr,
-                bool current = false)
+                Use use)
 {
     const Geo &G = g->geo;
-    const bool mx = g->mixed && !current;
+    const bool mx = g->mixed && use != Use::current;
     // a + b w + c w^2 (two rows per thread on a periodic grid: 0.2 us more
     // for the wrapped columns)
     const bool per = G.per[0] || G.per[1] || G.per[2];
     double pa = 0.42, pb = 0.05, pc = 0.004;
-    if (current) {
+    if (use == Use::current) {
         pb = 0.08;
         pc = 0.0;
     } else if (rpt == 2) {
@@ -488,8 +514,8 @@ double plane_us(const ks_grid *g, int TY, int rpt, int nthr, double wr,
         pb = mx ? 0.05 : 0.17;
         pc = 0.0;
     } else if (mx) {
-        pa = 0.45;
-        pb = 0.052;
+        pa = fp32_periodic(g, use) ? 0.55 : 0.45;
+        pb = fp32_periodic(g, use) ? 0.02 : 0.052;
         pc = 0.0;
     }
     const double halo = 1.0 + 0.1 * (8.0 / TY - 0.5);
@@ -501,9 +527,10 @@ double plane_us(const ks_grid *g, int TY, int rpt, int nthr, double wr,
 // Workgroups of w wavefronts and lds bytes that a CU holds: by registers four
 // or three wavefronts per SIMD with one row per thread (FP32, FP64), two with
 // two (and the current's); a workgroup takes ceil(w / 4) of every SIMD's.
-int cu_fit(bool mixed, int rpt, int w, size_t lds, bool current = false)
+int cu_fit(bool mixed, int rpt, int w, size_t lds, Use use)
 {
-    const int room = rpt == 2 || current ? 8 : (mixed ? 16 : 12);
+    const int room =
+        rpt == 2 || use == Use::current ? 8 : (mixed ? 16 : 12);
     return std::max(1, std::min(room / 4 / ((w + 3) / 4),
                                 (int)(kLdsBudget / lds)));
 }
@@ -511,11 +538,11 @@ int cu_fit(bool mixed, int rpt, int w, size_t lds, bool current = false)
 // The launch shape for ns states: the one with the least modelled time.  Few
 // states and small grids thus get short chunks of low tiles (24^3 x 4 states, 4
 // -> 240 workgroups: 40 -> 6 us per pass), large ones tall tiles of the whole
-// axis.  current: for the current's kernel (one row per thread, no projector
-// table).
-Shape pick_shape(const ks_grid *g, int ns, bool current = false)
+// axis.
+Shape pick_shape(const ks_grid *g, int ns, Use use)
 {
     const Geo &G = g->geo;
+    const bool current = use == Use::current;   // (no projector table)
     Shape best;
     double t_best = 1e300;
     for (int rpt = 1; rpt <= (current ? 1 : 2); ++rpt) {
@@ -533,16 +560,15 @@ Shape pick_shape(const ks_grid *g, int ns, bool current = false)
                 if (lds > kLdsBudget)
                     continue;
                 const long nwg = (long)ntile * ((G.nz + zc - 1) / zc) * ns;
-                const int fit = cu_fit(g->mixed && !current, rpt, w, lds,
-                                       current);
+                const int fit = cu_fit(g->mixed && !current, rpt, w, lds, use);
                 const long per_cu = std::min<long>(
                     fit, (nwg + kCUs - 1) / kCUs);
                 const long rounds = (nwg + kCUs * fit - 1) / (kCUs * fit);
                 const double t =
-                    rounds * (kStartUs +
-                              (zc + 4) * plane_us(g, TY, rpt, nthr,
-                                                  (double)(per_cu * w),
-                                                  current));
+                    rounds * (kStartUs + (zc + extra_planes(g, rpt, use)) *
+                                             plane_us(g, TY, rpt, nthr,
+                                                      (double)(per_cu * w),
+                                                      use));
                 if (t < t_best) {
                     t_best = t;
                     best.TY = TY;
@@ -568,8 +594,8 @@ Shape kept_shape(const ks_grid *g, int ns)
     std::atomic<uint64_t> &slot = g->shapes[ns];
     uint64_t v = slot.load(std::memory_order_relaxed);
     if (!v) {
-        const Shape s = ns > 0 ? pick_shape(g, ns)
-                               : pick_shape(g, g->stot, true);
+        const Shape s = ns > 0 ? pick_shape(g, ns, Use::call)
+                               : pick_shape(g, g->stot, Use::current);
         v = kDone | (uint64_t)s.rpt << 48 | (uint64_t)s.TY << 32 |
             (uint32_t)s.zchunk;
         slot.store(v, std::memory_order_relaxed);
@@ -586,7 +612,7 @@ int set_tiles(ks_grid *g, int TY, int zchunk, int rpt)
     const Geo &G = g->geo;
     g->auto_shape = TY <= 0 && zchunk <= 0 && rpt <= 0;
     if (g->auto_shape) {
-        const Shape s = pick_shape(g, g->stot);
+        const Shape s = pick_shape(g, g->stot, Use::steps);
         TY = s.TY;
         zchunk = s.zchunk;
         rpt = s.rpt;
@@ -2363,7 +2389,8 @@ void batch_shapes(const std::vector<ks_grid *> &grids, bool apart,
             lds = std::max(lds, lds_for(g, s.TY, s.zchunk));
             v.push_back(s);
         }
-        const int fit = cu_fit(grids[0]->mixed, rpt, nthr / 64, lds);
+        const int fit = cu_fit(grids[0]->mixed, rpt, nthr / 64, lds,
+                               Use::steps);
         // workgroups, and their mean of wavefronts at work
         double nwg = 0.0, waves = 0.0;
         std::vector<double> n, w;
@@ -2381,9 +2408,11 @@ void batch_shapes(const std::vector<ks_grid *> &grids, bool apart,
         for (size_t i = 0; i < v.size(); ++i) {
             const Shape &s = v[i];
             const double t =
-                kStartUs + (s.zchunk + 4) *
+                kStartUs + (s.zchunk + extra_planes(grids[i], s.rpt,
+                                                    Use::steps)) *
                                plane_us(grids[i], s.TY, s.rpt, nthr,
-                                        w[i] + (held - 1.0) * waves / nwg);
+                                        w[i] + (held - 1.0) * waves / nwg,
+                                        Use::steps);
             sum += n[i] * t;
             longest = std::max(longest, t);
         }
