@@ -280,10 +280,11 @@ int ks_energy(ks_grid *g, const void *d_psi, const double *d_vion, double t,
 /* Launch shape of the H.psi kernel: a workgroup owns tile_rows full x-rows
  * of one state and marches through zchunk z-planes; each thread marches
  * rows_per_thread (1 or 2) adjacent rows of the tile.  0 keeps the library's
- * choice for that parameter; with all three 0 (the default) a call on some
- * of the states takes the library's choice for that many states.  KS_E_ARG / KS_E_UNSUPPORTED if the shape does not fit (at
- * most 512 threads of nx * ceil(tile_rows / rows_per_thread), 160 KiB of
- * LDS, 16 halo loads per thread (8 with two rows)).  The workspace size does
+ * choice for that parameter; with all three 0 (the default) a call of
+ * ks_apply_h takes the library's choice for its number of states, and a batch
+ * chooses for its total work.  KS_E_ARG / KS_E_UNSUPPORTED if the shape does
+ * not fit (at most 512 threads of nx * ceil(tile_rows / rows_per_thread), 160
+ * KiB of LDS, 16 halo loads per thread (8 with two rows)).  The workspace size does
  * not depend on the shape.  States, dipoles and densities do not depend on
  * the shape; the norm diagnostics sum per-tile partials, so their last bits
  * do. */
@@ -300,7 +301,9 @@ int ks_set_overlap(ks_grid *g, int halves);
 
 /* out[0] = tile_rows, out[1] = zchunk, out[2] = workgroups per H.psi launch
  * over all states, out[3] = threads per workgroup, out[4] = rows per
- * thread. */
+ * thread: the shape of a propagator's passes.  In the library's own shape
+ * calls of ks_apply_h, batches and the current may run others (see
+ * ks_set_launch). */
 int ks_get_launch(const ks_grid *g, int out[5]);
 
 /* Kernel timing with HIP events on the grid's stream.  After

@@ -631,9 +631,9 @@ int set_tiles(ks_grid *g, int TY, int zchunk, int rpt)
                     lds_for(g, TY, std::min(G.nz, 16)) > kLdsDefault))
                 --TY;
         }
-        // two rows per thread allow 8 halo loads per thread and plane:
-        // the wrapped columns of a wide periodic row exceed that at any
-        // height, and one row per thread then takes it
+        // two rows per thread allow 8 halo loads per thread and plane; a
+        // tile that needs more (tall ones of short periodic rows, whose
+        // wrapped columns are loaded) takes one row per thread
         if (auto_rpt && rpt == 2 && !tile_ok(g, TY, rpt)) {
             rpt = 1;
             continue;
@@ -645,8 +645,9 @@ int set_tiles(ks_grid *g, int TY, int zchunk, int rpt)
                     "invalid for nx=%d ny=%d", TY, rpt, G.nx, G.ny);
     const int ntile_y = (G.ny + TY - 1) / TY;
     if (zchunk <= 0) {
-        // about two workgroups per CU over the launch, chunks of at least
-        // 32 planes (the z-halo of 8 planes stays a small fraction)
+        // (a caller's rows without a chunk) about two workgroups per CU
+        // over the launch, chunks of at least 32 planes: each loads its rows
+        // of the 8 planes around it as well and in FP64 marches four of them
         const long per_state = ntile_y;
         int nzc = (int)std::max<long>(1, 512 / std::max<long>(1, per_state *
                                                                   g->stot));

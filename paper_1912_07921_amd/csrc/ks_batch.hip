@@ -15,10 +15,10 @@ namespace ks {
 // (G, the grid size, a multiple of 8, so every index of one workgroup stays
 // on its XCD; the host sizes G to the item count, so each workgroup
 // usually takes one item) and decodes (job, item) from the job's item
-// offset (the H.psi items remapped per XCD within each job, below).  The pointers of Taylor pass p (exponential
-// e = (p-1)/4, term j = (p-1)%4 + 1) and the time of the pass come from the
-// job table and the job's device step counter, so a captured step replays
-// unchanged.
+// offset (the H.psi items remapped per XCD within each job, below).  The
+// pointers of Taylor pass p (exponential e = (p-1)/4, term j = (p-1)%4 + 1)
+// and the time of the pass come from the job table and the job's device step
+// counter, so a captured step replays unchanged.
 // ---------------------------------------------------------------------------
 // The job table, item offsets, A(t) tables and step counters do not change
 // while a batch kernel runs: read them through the constant address space

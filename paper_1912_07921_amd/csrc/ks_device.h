@@ -700,8 +700,9 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
     // planes.  The in-grid (or wrapped) halo rows are loaded per plane; the
     // wrapped columns of a periodic x axis are copies of the tile's own
     // values, written by the threads that hold them, or loaded where a row
-    // is shorter than both halves of the halo.  Loaded entry d goes to this thread when
-    // d = tid + i * nthr, i < HM.  hof: byte offset within a plane; hpk: LDS slot | phase id << 20 (id 40: no wrap) ----
+    // is shorter than both halves of the halo.  Loaded entry d goes to this
+    // thread when d = tid + i * nthr, i < HM.  hof: byte offset within a
+    // plane; hpk: LDS slot | phase id << 20 (id 40: no wrap) ----
     for (int t = tid; t < 2 * plane; t += nthr)
         buf0[t] = czero<V>();
     const bool xcopy = perx && nx >= 2 * kHalf;

@@ -558,7 +558,10 @@ constexpr long kGatherPlaneOrderMin = 8192;
 // 72 wavefronts, 8.7 + 4.4 us in two launches -> 8.6; 64^3 x 32, 2304, 13.1 +
 // 5.3 -> 13.6 (FP32 13.3 + 5.1 -> 11.5); 48^3 x 64, 3072, 15.6 + 4.6 -> 18.6;
 // 72x60x66 x 40, 3600, 16.1 + 5.3 -> 22.0.  Four projectors: 7.5, 11.5 (FP32
-// 10.1), 13.7 us, and 13.8 + 5.7 us in two launches at 3600.
+// 10.1), 13.7 us; by events, two launches against one: 60^3 x 12, 3348, 20.7
+// and 21.0, 64^3 x 56, 4032, 22.0 and 21.2, 48^3 x 36, 5184, 24.3 and 27.3.
+// (Nine projectors on spheres of 16 chunks, two rounds of the workgroup's
+// wavefronts, still gain at 6144: 32.7 and 30.2.)
 constexpr long kGatherSphereMax = 3072, kGatherSphereMax4 = 4096;
 
 template <int NP>

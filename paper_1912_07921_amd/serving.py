@@ -32,14 +32,15 @@ from . import ks
 
 
 def set_serving_launch(grid, spec):
-    """Launch shape of a served job: the default tile rows with z-chunks of
-    the whole axis.  With many jobs resident the batch has work items to
-    spare, and every z-chunk re-reads the 8 planes around it (saturated
-    serving mix, FP64: 10 % shorter steps than the single-grid default of up
-    to two chunks).  States and dipoles do not depend on the shape; the norm
-    diagnostics (sums of per-tile partials) do in their last bits, so a
-    request is compared with its lone run in this same shape.  A grid whose
-    LDS cannot hold the whole-axis chunk keeps its default."""
+    """Launch shape of a served job: the tallest tiles (512 threads, two rows
+    per thread in FP64) with z-chunks of the whole axis.  With many jobs
+    resident the batch has work items to spare, and every z-chunk loads its
+    rows of the 8 planes around it again (saturated serving mix, FP64: 10 %
+    shorter steps than in up to two chunks).  It is the job's own shape, the
+    same in every batch and alone: states and dipoles do not depend on it; the
+    norm diagnostics (sums of per-tile partials) do in their last bits, so a
+    request is compared with its lone run in this shape.  A grid whose LDS
+    cannot hold the whole-axis chunk keeps its default."""
     try:
         grid.set_launch(0, spec.n[2])
     except ks.KSError:
