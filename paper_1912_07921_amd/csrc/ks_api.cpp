@@ -2264,7 +2264,6 @@ struct ks_batch {
     int ndip = 0, nnorm = 0, max_ns = 0;
     // norm partials of the jobs whose launch shape is the batch's choice
     NormTiles *d_ntile = nullptr;
-    int *d_ntile_off = nullptr;
     int nntile = 0, blk_ntile = 0, nthr_ntile = 64;
     std::vector<int> steps_done;
     bool use_graph = true;
@@ -2360,6 +2359,9 @@ void batch_shapes(const std::vector<ks_grid *> &grids, bool apart,
         int threads, chunks;     // 0: the grids' own shapes
     };
     double best = 1e300;
+    const bool choose =
+        std::any_of(grids.begin(), grids.end(),
+                    [](const ks_grid *g) { return g->auto_shape; });
     for (const Rule r : {Rule{0, 0}, Rule{512, 1}, Rule{512, 2}, Rule{512, 3},
                          Rule{256, 2}}) {
         std::vector<Shape> v;
@@ -2389,6 +2391,10 @@ void batch_shapes(const std::vector<ks_grid *> &grids, bool apart,
             nthr = std::max(nthr, hpsi_threads(G.nx, s.TY, s.rpt));
             lds = std::max(lds, lds_for(g, s.TY, s.zchunk));
             v.push_back(s);
+        }
+        if (!choose) {
+            *out = v;
+            return;
         }
         const int fit = cu_fit(grids[0]->mixed, rpt, nthr / 64, lds,
                                Use::steps);
@@ -2478,8 +2484,8 @@ int batch_enqueue_step(ks_batch *b)
                                   st));
     }
     KS_HIP(launch_dipole_finalize_batch(b->d_dip, b->ndip, st));
-    KS_HIP(launch_norm_tiles_batch(b->d_ntile, b->d_ntile_off, b->nntile,
-                                   b->blk_ntile, b->nthr_ntile, st));
+    KS_HIP(launch_norm_tiles_batch(b->d_ntile, b->nntile, b->blk_ntile,
+                                   b->nthr_ntile, st));
     KS_HIP(launch_norm_finalize_batch(b->d_norm, b->nnorm, b->max_ns, st));
     KS_HIP(launch_step_advance(b->d_steps, (int)b->grids.size(), st));
     return KS_OK;
@@ -2742,7 +2748,6 @@ int ks_batch_create(const ks_job *jobs, int njobs, void *stream,
         std::vector<DipJob> dip;
         std::vector<NormJob> nrm;
         std::vector<NormTiles> ntl;
-        std::vector<int> ontl(1, 0);
         long blk_ntl = 0;
         for (int i = 0; i < njobs; ++i) {
             ks_grid *g = b->grids[i];
@@ -2801,9 +2806,9 @@ int ks_batch_create(const ks_job *jobs, int njobs, void *stream,
                     t.zchunk = g->zchunk;
                     t.ntile_y = g->ntile_y;
                     t.nzc = g->nzc;
+                    t.first = (int)std::min(blk_ntl, (1L << 31) - 1);
                     ntl.push_back(t);
                     blk_ntl += (long)n.ntiles * g->stot;
-                    ontl.push_back((int)std::min(blk_ntl, (1L << 31) - 1));
                     b->nthr_ntile = std::max(
                         b->nthr_ntile,
                         hpsi_threads(g->geo.nx, g->TY, g->rpt));
@@ -2820,7 +2825,12 @@ int ks_batch_create(const ks_job *jobs, int njobs, void *stream,
         b->blk_pred = opred.back();
         b->blk_end = oend.back();
         b->nntile = (int)ntl.size();
-        b->blk_ntile = ontl.back();
+        b->blk_ntile = (int)blk_ntl;
+        if (!ntl.empty()) {
+            NormTiles end;
+            end.first = b->blk_ntile;
+            ntl.push_back(end);
+        }
         b->ndip = (int)dip.size();
         b->nnorm = (int)nrm.size();
         auto put = [&](auto **dst, const auto &v) -> int {
@@ -2837,8 +2847,7 @@ int ks_batch_create(const ks_job *jobs, int njobs, void *stream,
             (rc = put(&b->d_dpred_off, opred)) ||
             (rc = put(&b->d_dend, dend)) || (rc = put(&b->d_dend_off, oend)) ||
             (rc = put(&b->d_dip, dip)) || (rc = put(&b->d_norm, nrm)) ||
-            (rc = put(&b->d_ntile, ntl)) ||
-            (rc = put(&b->d_ntile_off, ontl))) {
+            (!ntl.empty() && (rc = put(&b->d_ntile, ntl)))) {
             ks_batch_destroy(b);
             return rc;
         }

@@ -242,11 +242,12 @@ struct NormTiles {
     double *part = nullptr;          // [ns][ntile_y * nzc]
     int nx = 1, ny = 1, nz = 1, TY = 1, rpt = 1, zchunk = 1, ntile_y = 1,
         nzc = 1;
+    int first = 0;                   // its first launch block
 };
+// jobs[njobs].first = nblocks
+hipError_t launch_norm_tiles_batch(const NormTiles *jobs, int njobs,
+                                   int nblocks, int nthr, hipStream_t st);
 // blk_off[j] = first launch block of job j (blk_off[njobs] = nblocks)
-hipError_t launch_norm_tiles_batch(const NormTiles *jobs, const int *blk_off,
-                                   int njobs, int nblocks, int nthr,
-                                   hipStream_t st);
 hipError_t launch_density_batch(const DArgs *args, const int *blk_off,
                                 int njobs, int nblocks, hipStream_t st);
 hipError_t launch_dipole_finalize_batch(const DipJob *jobs, int njobs,

@@ -263,16 +263,16 @@ __global__ __launch_bounds__(64) void k_norm_finalize_batch(
 // final pass (hpsi_item), so that partials and norms have the same bits
 // whatever shape a batch runs.  One read of the states, after eight passes.
 __global__ __launch_bounds__(512) void k_norm_tiles_batch(
-    const NormTiles *jobs, const int *blk_off, int njobs)
+    const NormTiles *jobs, int nblocks)
 {
     __shared__ double sbuf[8];
     int j = 0;
-    for (int b = blockIdx.x; b < blk_off[njobs]; b += gridDim.x) {
-        while (b >= blk_off[j + 1])
+    for (int b = blockIdx.x; b < nblocks; b += gridDim.x) {
+        while (b >= jobs[j + 1].first)
             ++j;
         const NormTiles J = jobs[j];
         const int ntiles = J.ntile_y * J.nzc;
-        const int w = b - blk_off[j];
+        const int w = b - J.first;
         const int sl = w / ntiles, tile = w - sl * ntiles;
         const int zc = tile / J.ntile_y, y0 = (tile - zc * J.ntile_y) * J.TY;
         const int rpt = min(J.rpt, J.TY);
@@ -795,15 +795,14 @@ hipError_t launch_norm_finalize_batch(const NormJob *jobs, int njobs,
     return hipGetLastError();
 }
 
-hipError_t launch_norm_tiles_batch(const NormTiles *jobs, const int *blk_off,
-                                   int njobs, int nblocks, int nthr,
-                                   hipStream_t st)
+hipError_t launch_norm_tiles_batch(const NormTiles *jobs, int njobs,
+                                   int nblocks, int nthr, hipStream_t st)
 {
     if (njobs <= 0 || nblocks <= 0)
         return hipSuccess;
     // (2^22 workgroups of 512 threads at most)
     hipLaunchKernelGGL(k_norm_tiles_batch, dim3(std::min(nblocks, 1 << 22)),
-                       dim3(nthr), 0, st, jobs, blk_off, njobs);
+                       dim3(nthr), 0, st, jobs, nblocks);
     return hipGetLastError();
 }
 
