@@ -1,8 +1,8 @@
 """Gram matrix of grids of few points, whose slices (at least 256 points) are
 few: against torch at point counts around the slices' edges, and the time of
 1728 points of 500 states against eight times as many points, which fill the
-chip (three tenths of it or more means that the small grid's workgroups are too
-few: 36 tiles of states need six slices rather than three)."""
+chip (a quarter of it with six slices for the 36 tiles of states, nearly half
+with the three of at least 512 points)."""
 import time
 
 import numpy as np
@@ -50,4 +50,4 @@ def test_gram_of_few_points_fills_the_chip():
             best[n] = min(best.get(n, 1.0), time.perf_counter() - t0)
         g.close()
     print({k: round(1e6 * v) for k, v in best.items()}, "us")
-    assert best[12] < 0.3 * best[24], best
+    assert best[12] < 0.36 * best[24], best
