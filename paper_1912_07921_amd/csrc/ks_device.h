@@ -507,17 +507,22 @@ __device__ __forceinline__ int xcd_remap(int L, int nblk)
 // Every tap is one FMA with a coefficient that carries -1/2 c_m / h^2, from
 // the smallest weight to the largest: half the rounding error of pairwise
 // sums.  The FP32 kernels keep a column of nine values and the order of their
-// sums.  Every access is a raw buffer access with a constant per-thread offset
-// and the plane in the scalar offset.
+// sums.  So do FP64 tiles of one row (rows above 256 points; eight or more halo
+// loads per thread), with the split star's order of sums: their neighbours are
+// all halo rows, which the split star asks for while the tiles that own them
+// do, where the column has asked four planes before (400 x 24 x 30 x 6 with A
+// along every axis 60.4 -> 51.3 us a pass, 512 x 20 x 40 x 8 78 -> 69, 300 x 90
+// x 64 x 16 640 -> 562).  Every access is a raw buffer access with a constant
+// per-thread offset and the plane in the scalar offset.
 // What bounds it: large launches memory (128^3 x 64 states FP64 term pass, 6.0
 // GB through the L2 in 1.05 ms = 5.7 TB/s, where a plain copy reaches 6.6;
 // without the x taps 1.02 ms), launches of few states the chain of barrier,
 // LDS reads, FMAs and loads of each plane (~0.6 us with one row per thread,
 // whatever is loaded), which is why those get short chunks of low tiles.
 // Loads run PF planes ahead of their use: 2, or 1 in the FP64 kernels with
-// two rows per thread, whose registers hold no second set (64^3 x 32, one row:
-// 80 -> 72 us with 2; two rows: 70 -> 127 us, spilled).  The KB term V_NL in
-// is precomputed on the hull rows
+// two rows per thread or the column, whose registers hold no second set (64^3 x
+// 32, one row: 80 -> 72 us with 2; two rows: 70 -> 127 us, spilled; the column
+// 52 -> 85 us).  The KB term V_NL in is precomputed on the hull rows
 // (k_kbapply) and added with one coalesced read.
 // ---------------------------------------------------------------------------
 extern __shared__ double2 smem_d2[];
@@ -581,9 +586,11 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
     }
     const int z0 = zc * a.zchunk;
     const int z1 = min(nz, z0 + a.zchunk);
-    // FP64 scatters plane z's z taps to pending outputs, FP32 gathers them
-    // from a column of nine values (below)
-    constexpr bool SC = sizeof(R) == 8;
+    // FP64 scatters plane z's z taps to pending outputs; FP32, and FP64 tiles
+    // of one row, gather them from a column of nine values (below)
+    constexpr bool F64 = sizeof(R) == 8;
+    constexpr bool SC = F64 && !(RPT == 1 && HM >= 8 && !CUR && !ENE);
+    constexpr bool COL64 = F64 && !SC;
     const int zend = SC && !CUR ? z1 + 4 : z1;      // planes marched
 
     const int plane = (TY + 2 * kHalf) * RS;
@@ -645,8 +652,8 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
         return v;
     };
     // the first planes of the column: they are in flight during the setup.
-    // FP64: p[r][s] holds plane z < z0 with (z - z0) & 3 == s; FP32: q[r][m]
-    // holds plane z + m - 4.
+    // Split star: p[r][s] holds plane z < z0 with (z - z0) & 3 == s; column:
+    // q[r][m] holds plane z + m - 4.
     V p[RPT][4], q[RPT][9], c[RPT];
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
@@ -778,7 +785,7 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
     };
     // own values and halo of one plane into an LDS buffer
     auto put_own = [&](V *buf) {
-        const int rs = fresh(RS);
+        const int rs = COL64 ? RS : fresh(RS);
 #pragma unroll
         for (int r = 0; r < RPT; ++r)
             if (valid[r])
@@ -786,7 +793,7 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
         if (xcopy && (x < kHalf || x >= nx - kHalf)) {
             // wrap by +1 (phase 41) to the right of the row, by -1 (39) to
             // its left
-            const int w = fresh(nx);
+            const int w = COL64 ? nx : fresh(nx);
             const bool left = x < kHalf;
             const V ph = sPh[left ? 41 : 39];
             V *d = buf + own + (left ? w : -w);
@@ -797,7 +804,7 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
         }
     };
     auto put_halo = [&](V *buf, int i, V v) {
-        const int o = fresh(0);
+        const int o = COL64 ? 0 : fresh(0);
         if (hof[i] != kBufNone) {
             const int pid = hpk[i] >> 20;
             if (pid != 40)
@@ -808,7 +815,7 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
 
     // ---- plane z0: halo, potential, KB term; with two planes of lead also
     // plane z0 + 1 ----
-    constexpr int PF = !SC || RPT == 1 ? 2 : 1;
+    constexpr int PF = !F64 || (SC && RPT == 1) ? 2 : 1;
     constexpr int NS = SC ? PF : 2 * PF;   // sets of potential and KB term
     // plane of the own rows loaded for plane zq of the column (-1: none)
     auto ahead = [&](int zq) -> int {
@@ -869,7 +876,7 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
     R LC[5], GD[5];
 #pragma unroll
     for (int m = 1; m <= 4; ++m) {
-        if constexpr (SC) {
+        if constexpr (F64) {
 #pragma unroll
             for (int ax = 0; ax < 3; ++ax) {
                 CL[ax][m] = a.cl[ax][m - 1];
@@ -882,7 +889,7 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
             GD[m] = (R)kGrad[m];
         }
     }
-    const R c0 = SC ? (R)a.c0 : (R)0;
+    const R c0 = F64 ? (R)a.c0 : (R)0;
     const R ih2x = (R)(1.0 / (a.geo.h[0] * a.geo.h[0]));
     const R ih2y = (R)(1.0 / (a.geo.h[1] * a.geo.h[1]));
     const R ih2z = (R)(1.0 / (a.geo.h[2] * a.geo.h[2]));
@@ -962,7 +969,7 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
             }
         if (z < z1) {
             __syncthreads();
-            const int rs = fresh(RS);
+            const int rs = COL64 ? RS : fresh(RS);
             const V *rp = cur + own;
             V yv[RPT + 8];        // y neighbours of all rows: rows -4 ..
 #pragma unroll
@@ -1010,7 +1017,7 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
                          [&](int m) { return p[r][(PH + 4 - m) & 3]; });
                     continue;
                 }
-                if constexpr (!SC) {
+                if constexpr (!F64) {
                     // the FP32 sums keep their order, and so their bits:
                     // pairs of taps, the weights apart from 1 / h^2
                     V gx = czero<V>(), gy = czero<V>(), gz = czero<V>();
@@ -1049,7 +1056,7 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
                 for (int m = 4; m >= 1; --m) {
                     const V xn = rx[-m], xp = rx[m];
                     const V yn = yv[r + 4 - m], yp = yv[r + 4 + m];
-                    const V zn = p[r][(PH + 4 - m) & 3];
+                    const V zn = SC ? p[r][(PH + 4 - m) & 3] : q[r][4 - m];
                     sx = cfma(CL[0][m], xn, sx);
                     sy = cfma(CL[1][m], yn, sy);
                     sz = cfma(CL[2][m], zn, sz);
@@ -1068,9 +1075,26 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
                     // -i A.grad
 #pragma unroll
                     for (int m = 4; m >= 1; --m)
-                        g = cfma(-CG[2][m], p[r][(PH + 4 - m) & 3], g);
+                        g = cfma(-CG[2][m],
+                                 SC ? p[r][(PH + 4 - m) & 3] : q[r][4 - m], g);
                     h.x += g.y;
                     h.y -= g.x;
+                }
+                if constexpr (!SC) {
+                    // the upper z taps from the column, in the order in which
+                    // the split star adds them
+#pragma unroll
+                    for (int m = 1; m <= 4; ++m) {
+                        const V zp = q[r][4 + m];
+                        h = cfma(CL[2][m], zp, h);
+                        if constexpr (GRAD) {
+                            h.x = rfma(CG[2][m], zp.y, h.x);
+                            h.y = rfma(-CG[2][m], zp.x, h.y);
+                        }
+                    }
+                    done[r] = h;
+                    cdone[r] = cc;
+                    continue;
                 }
                 o[r][PH] = h;
             }
@@ -1083,7 +1107,7 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
                 const unsigned off = off_of(r, sizeof(OutT));
                 // FP64: potential and KB term of the finished point
                 V hp = done[r];
-                if constexpr (SC)
+                if constexpr (F64)
                     hp = cadd(cfma((R)(sv[UV][r] + Avec.w), cdone[r], hp),
                               skb[UV][r]);
                 if constexpr (ENE) {
@@ -1109,7 +1133,7 @@ __device__ __forceinline__ void hpsi_item(const HArgs &a, const int w,
                                           8.0 * t3.x + 16.0 * (double)t4.x;
                         const double pi = bb.y + 2.0 * u1.y + 4.0 * u2.y +
                                           8.0 * t3.y + 16.0 * (double)t4.y;
-                        part = w_occ * (pr * pr + pi * pi);
+                        part = w_occ * abs2f(pr, pi);
                     } else {
                         const double sq = abs2f(re, im);
                         part = w_occ * sq;
