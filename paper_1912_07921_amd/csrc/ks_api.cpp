@@ -2243,7 +2243,8 @@ struct ks_batch {
     std::vector<ks_job> jobs;
     std::vector<JobDev> hjobs;
     hipStream_t stream = nullptr;
-    bool mixed = false, grad = false;
+    bool mixed = false;
+    int grad = 0;   // gradient term: 0 none, 1 every axis, 2 z only
     int hm = 2, rpt = 1, nthr = 64;
     size_t lds = 0;
     int grid_hpsi = 0, grid_proj = 0;
@@ -2568,8 +2569,12 @@ int ks_batch_create(const ks_job *jobs, int njobs, void *stream,
         J.dt = jobs[i].dt;
         J.step = wsp<int>(g, g->lay.step);
         b->hjobs.push_back(J);
-        if (g->laser[0] != 0.0)
-            b->grad = true;
+        if (g->laser[0] != 0.0) {
+            if (g->laser[3] != 0.0 || g->laser[4] != 0.0)
+                b->grad = 1;
+            else if (b->grad == 0)
+                b->grad = 2;
+        }
         b->rpt = std::max(b->rpt, J.h.rpt);
         b->nthr = std::max(b->nthr,
                            hpsi_threads(g->geo.nx, J.h.TY, J.h.rpt));

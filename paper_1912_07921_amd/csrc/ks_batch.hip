@@ -210,24 +210,29 @@ static hipError_t go_hpsi_batch(const BArgs &b, int hm, int rpt, int nthr,
 }
 
 template <class R, class InT, class TT, int MODE>
-static hipError_t go_hpsi_batch_g(const BArgs &b, bool grad, int hm, int rpt,
+static hipError_t go_hpsi_batch_g(const BArgs &b, int grad, int hm, int rpt,
                                   int nthr, size_t lds, int grid,
                                   hipStream_t st)
 {
-    return grad ? go_hpsi_batch<R, InT, TT, MODE, 1>(b, hm, rpt, nthr,
-                                                        lds, grid, st)
-                : go_hpsi_batch<R, InT, TT, MODE, 0>(b, hm, rpt, nthr,
-                                                         lds, grid, st);
+    if (grad == 1)
+        return go_hpsi_batch<R, InT, TT, MODE, 1>(b, hm, rpt, nthr, lds,
+                                                  grid, st);
+    // every laser along z: a third of the gradient's taps, as in the lone
+    // launch (FP32, 3 periodic jobs of 80^3 x 16 9.09 -> 8.73 ms for 4 steps)
+    return grad == 2 ? go_hpsi_batch<R, InT, TT, MODE, 2>(b, hm, rpt, nthr,
+                                                          lds, grid, st)
+                     : go_hpsi_batch<R, InT, TT, MODE, 0>(b, hm, rpt, nthr,
+                                                          lds, grid, st);
 }
 
 // Compiled twice like the single-grid H.psi file: part 0 holds the FP64
 // pass kernels and everything else, part 1 the mixed-precision pass kernels.
-hipError_t launch_pass_batch_mixed(const BArgs &b, bool grad, int hm, int rpt,
+hipError_t launch_pass_batch_mixed(const BArgs &b, int grad, int hm, int rpt,
                                    int nthr, size_t lds, int grid,
                                    hipStream_t st);
 
 #if KS_HPSI_PART == 0
-hipError_t launch_pass_batch(bool mixed, const BArgs &b, bool grad, int hm,
+hipError_t launch_pass_batch(bool mixed, const BArgs &b, int grad, int hm,
                              int rpt, int nthr, size_t lds, int grid,
                              hipStream_t st)
 {
@@ -244,7 +249,7 @@ hipError_t launch_pass_batch(bool mixed, const BArgs &b, bool grad, int hm,
                         b, grad, hm, rpt, nthr, lds, grid, st);
 }
 #else
-hipError_t launch_pass_batch_mixed(const BArgs &b, bool grad, int hm, int rpt,
+hipError_t launch_pass_batch_mixed(const BArgs &b, int grad, int hm, int rpt,
                                    int nthr, size_t lds, int grid,
                                    hipStream_t st)
 {

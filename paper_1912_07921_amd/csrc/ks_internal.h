@@ -302,7 +302,8 @@ struct BArgs {
 };
 
 int batch_items(int kind, const JobDev &J);
-hipError_t launch_pass_batch(bool mixed, const BArgs &b, bool grad, int hm,
+// grad: 0 no laser, 1 any, 2 along z only
+hipError_t launch_pass_batch(bool mixed, const BArgs &b, int grad, int hm,
                              int rpt, int nthr, size_t lds, int grid,
                              hipStream_t st);
 hipError_t launch_projectors_batch(bool mixed, const BArgs &bg,
