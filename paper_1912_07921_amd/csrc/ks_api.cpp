@@ -2363,6 +2363,10 @@ void batch_shapes(const std::vector<ks_grid *> &grids, bool apart,
     const bool choose =
         std::any_of(grids.begin(), grids.end(),
                     [](const ks_grid *g) { return g->auto_shape; });
+    const bool periodic =
+        std::any_of(grids.begin(), grids.end(), [](const ks_grid *g) {
+            return g->geo.per[0] || g->geo.per[1] || g->geo.per[2];
+        });
     for (const Rule r : {Rule{0, 0}, Rule{512, 1}, Rule{512, 2}, Rule{512, 3},
                          Rule{256, 2}}) {
         std::vector<Shape> v;
@@ -2428,6 +2432,11 @@ void batch_shapes(const std::vector<ks_grid *> &grids, bool apart,
                                      : sum / (kCUs * fit) + 0.4 * longest;
         if (apart && !own)
             t *= 1.03;
+        // with periodic jobs, which load every halo row, large workgroups
+        // wait longer at their barriers (512 threads and halves against 256
+        // and halves: 2 to 20 % longer steps in 14 such batches)
+        if (periodic && r.threads == 512)
+            t *= 1.1;
         if (t < best) {
             best = t;
             *out = v;
